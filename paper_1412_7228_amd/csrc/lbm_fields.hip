@@ -123,7 +123,9 @@ struct ObsSum {
 // are a quarter of the arithmetic, and a cell can only raise the maximum if
 // (j + F/2)^2 > max rho^2 (up to rounding: the bound is lowered by 1e-12), so a
 // wave divides only where one of its lanes passes that test against the
-// wave's maximum, on 4 rows of 35 or so.
+// wave's maximum, on 4 rows of 35 or so.  Squares that are not normal numbers
+// (densities beyond 1e+-154, momenta below 1e-154) decide nothing: such cells
+// divide, but for those whose momentum is zero.
 __device__ __forceinline__ void accumulate_cell(ObsSum& s, bool own, double r, double U, double Fx, double Fy,
                                                 double jx, double jy) {
   const double mx = jx + 0.5 * Fx, my = jy + 0.5 * Fy;
@@ -136,7 +138,12 @@ __device__ __forceinline__ void accumulate_cell(ObsSum& s, bool own, double r, d
     s.n_domain += U <= 0.0 ? 0u : 1u;               // U > 0 (or NaN)
     s.n_bad += r > 0.0 && isfinite(r) ? 0u : 1u;    // rho <= 0 or not finite
   }
-  if (__any(own && mx * mx + my * my > s.wave_v2 * (r * r) * (1.0 - 1e-12))) {
+  const double m2 = mx * mx + my * my, r2 = r * r;
+  constexpr int kNormal = 0x100 | 0x008;  // v_cmp_class: positive, negative normal
+  const bool m_normal = __builtin_amdgcn_class(m2, kNormal), r_normal = __builtin_amdgcn_class(r2, kNormal);
+  const bool above = m2 > s.wave_v2 * r2 * (1.0 - 1e-12) || !r_normal;
+  if (__any(own && (above || !m_normal)) &&
+      __any(own && (above || (!m_normal && (mx != 0.0 || my != 0.0))))) {
     const double vx = mx / r, vy = my / r;
     const double v2 = vx * vx + vy * vy;
     if (own && v2 == v2) s.v2 = fmax(s.v2, v2);

@@ -66,3 +66,19 @@ def test_batch_observables_reduce_each_domain(lbm, precision, copies):
         obs = b.observables()
         for i in sorted({0, 1, 2, 3, 4, 5, 6, len(sizes) - 1}):
             _check(obs[i], *(b.field(i, k) for k in ("rho", "ux", "uy")))
+
+
+@pytest.mark.parametrize("scale,u", [(1e160, 1e-2), (1e-160, 1e-2), (1.0, 1e-80), (1e-120, 1e-60)])
+def test_largest_velocity_where_squares_leave_the_range(lbm, scale, u):
+    """max_u of states whose squared momenta or densities overflow or underflow (the velocities do
+    not), the larger velocities in the later rows of a tile; the bound of _check (8 ulp)."""
+    print(f"[gpu-case] observables at densities of {scale} and velocities of {u}", flush=True)
+    nx, ny = 70, 60
+    g = np.random.default_rng(7)
+    rho = scale * (1.0 + 0.1 * g.random((ny, nx)))
+    ramp = u * np.arange(1, ny + 1)[:, None] / ny
+    lat = lbm.Lattice(dict(nx=nx, ny=ny, eos="ideal", precision="fp64"))
+    lat.init_field(rho, ramp * (1.0 + 0.1 * g.random((ny, nx))), -ramp * g.random((ny, nx)))
+    f = lat.fields()
+    want = np.hypot(f["ux"], f["uy"]).max()
+    assert abs(lat.observables(check=False)["max_u"] - want) <= 8 * 2.0 ** -52 * want
