@@ -1203,6 +1203,7 @@ lbm_status batch_layout(lbm_batch* b) {
     std::vector<DomainSize> sizes(b->n);
     for (int d = 0; d < b->n; ++d) sizes[d] = {b->g[d].nx, b->g[d].ny};
     b->blocks = plan_batch(sizes, b->prec == LBM_FP32 ? 4 : 8, b->cus);
+    if (b->blocks.tiles_us_per_step < b->blocks.us_per_step) b->blocks = BatchBlocks{};
     b->nblocks = b->n;
     if (b->blocks.k > 0 && !b->blocks.whole) {
       const size_t bb = batch_block_bytes();

@@ -20,6 +20,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <tuple>
 #include <vector>
 
 #include "lbm_internal.h"
@@ -174,31 +175,147 @@ struct BatchBlocks {
   bool whole = false;
   BlockShape shape{};
   std::vector<int> ntx, nty;
-  double us_per_step = 1e300;
+  double us_per_step = 1e300, tiles_us_per_step = 1e300;  // modelled; the tiles' of the default shape
 };
 
 struct DomainSize {
   int nx, ny;
 };
 
+// The domains of one size together, larger sizes first: what a plan sees, whatever
+// the order of the batch.
+struct DomainClass {
+  DomainSize size;
+  double count;
+  double cells() const { return (double)size.nx * size.ny; }
+  double weight() const { return count * (cells() + 512.0); }  // 512: a block's cost of being there
+};
+
+// The classes of a batch; of[d] is the class of domain d.
+inline std::vector<DomainClass> domain_classes(const std::vector<DomainSize>& dom, std::vector<int>* of) {
+  std::vector<int> order(dom.size());
+  for (size_t d = 0; d < dom.size(); ++d) order[d] = (int)d;
+  auto key = [&](int d) { return std::make_tuple(-(long long)dom[d].nx * dom[d].ny, dom[d].nx); };
+  std::sort(order.begin(), order.end(), [&](int a, int b) { return key(a) < key(b); });
+  std::vector<DomainClass> classes;
+  of->resize(dom.size());
+  for (int d : order) {
+    if (classes.empty() || classes.back().size.nx != dom[d].nx || classes.back().size.ny != dom[d].ny)
+      classes.push_back({dom[d], 0.0});
+    classes.back().count += 1.0;
+    (*of)[d] = (int)classes.size() - 1;
+  }
+  return classes;
+}
+
+// At most `most` classes that stand for all of them: the classes in shares of
+// equal weight, each share by the class at its middle.
+inline std::vector<DomainClass> sample_classes(const std::vector<DomainClass>& classes, int most) {
+  if ((int)classes.size() <= most) return classes;
+  double all = 0.0;
+  for (const auto& q : classes) all += q.weight();
+  std::vector<DomainClass> out;
+  double from = 0.0;  // weight before class i
+  size_t i = 0;
+  for (int s = 0; s < most; ++s) {
+    const double middle = (s + 0.5) / most * all;
+    while (i + 1 < classes.size() && from + classes[i].weight() < middle) from += classes[i++].weight();
+    out.push_back({classes[i].size, all / most / (classes[i].cells() + 512.0)});
+  }
+  return out;
+}
+
 // Shapes of the whole-domain kernel: the smallest that holds the largest
 // domain (small workgroups share a CU).
 constexpr BlockShape kWholeShapes[] = {{256, 1}, {512, 1}, {1024, 1}, {512, 4}};
 
+// The division of a domain of least work; the caller's sums over its blocks.
+struct BlockCut {
+  int ntx = 0, nty = 0;
+  double work = 1e300, cells = 0.0;
+};
+
+inline BlockCut cut_domain(const BlockCost& c, const DomainSize& d, BlockShape s, int k, int finer) {
+  const int halo = 2 * (2 * k - 1);
+  BlockCut best;
+  for_block_widths(d.nx, [&](int ntx) {
+    const int fewest = block_rows(d.nx, d.ny, ntx, k, s.threads * s.cells);
+    if (fewest == 0) return;
+    const int nty = std::min(d.ny, fewest * finer);
+    const int w = (d.nx + ntx - 1) / ntx, h = (d.ny + nty - 1) / nty;
+    const BlockCut q{ntx, nty, ntx * nty * block_work(c, w + halo, h + halo, k),
+                     (double)ntx * nty * ((double)(w + halo) * (h + halo) + (double)w * h)};
+    if (q.work + c.hide * c.moved * q.cells < best.work + c.hide * c.moved * best.cells) best = q;
+  });
+  return best;
+}
+
+// What a launch of k steps over all of a batch costs, its domains' blocks added up.
+// Blocks of domains far smaller than a workgroup wait twice for their start and chain,
+// shared by the r workgroups of a CU (2,000 domains of 3^2 beside a 1500^2).
+//
+// A batch whose two buffers pass the 256 MB last-level cache moves its cells at the
+// rate of HBM: a launch takes at least its loads and stores at 4.5 TB/s (FP32) or
+// 5.0 (FP64), the halos' second reads included (4096^2 in blocks of 38 x 32, one
+// step: 1.28 GB in 272 us; FP64 24 x 20, one step 2.65 GB in 497; 3000^2 at two
+// steps 766 MB in 174, where the fitted model says 149).  And beyond
+// block_beyond_cache the FP64 model is 1.16 times what is measured (1448^2 to 4096^2,
+// 60 to 240 domains of 200^2, uneven ones: 1.13 to 1.19).
+struct BatchLaunchCost {
+  int es, k, resident;
+  double blocks = 0.0, work = 0.0, cells = 0.0, busy = 0.0;
+  void add(const BlockCut& q, double count) {
+    const BlockCost c = block_cost(es);
+    const double n = (double)q.ntx * q.nty;
+    blocks += count * n;
+    work += count * q.work;
+    cells += count * q.cells;
+    busy += count * std::max(q.work + (resident > 1 ? c.hide : 1.0) * c.moved * q.cells,
+                             n * 2.0 * (c.start + k * c.step) / resident);
+  }
+  double us(double all_cells, int cus) const {
+    const BlockCost c = block_cost(es);
+    const double q = std::ceil(blocks / cus);
+    double t = q <= resident ? block_launch_time(c, k, q, work / blocks, cells / blocks, resident)
+                             : c.start + q * busy / blocks;
+    if (block_beyond_cache(es, (long long)all_cells) && es == 8) t *= 0.86;
+    if (all_cells * 18 * es > 256e6) t = std::max(t, cells * 9 * es / (es == 4 ? 4.5e6 : 5.0e6));
+    return t;
+  }
+};
+
+// A two-step launch of the marching tiles of the default shape (256 lanes by 16
+// rows, 250 columns stored): so much a tile and so much a cell, and at least a
+// tile's chain of rows.  Fitted to 34 batches (one domain of 1024^2 to 4,000 of
+// 50^2) within 5% rms.
+inline double batch_tiles_time(const std::vector<DomainClass>& classes, int es) {
+  const int w = 256 - kStep2Halo;
+  double tiles = 0.0, cells = 0.0;
+  for (const auto& q : classes) {
+    tiles += q.count * ((q.size.nx + w - 1) / w) * ((q.size.ny + 15) / 16);
+    cells += q.count * q.cells();
+  }
+  return es == 4 ? std::max(35.0, 10.4 + 31.5e-3 * tiles + 8.1e-6 * cells)
+                 : std::max(41.0, 21.3 + 79.5e-3 * tiles + 11.9e-6 * cells);
+}
+
+// Steps and shape from at most 16 classes that stand for the batch, then every
+// class's division, whose sum is the plan's time; the caller takes the tiles where
+// they take less.  (Sampled by their place in the
+// batch, 40 domains of 3^2 before a 2000^2 and a 3000^2 chose for the small ones:
+// 1,790 us a step, where the tiles take 112 and this plan 107.)
 inline BatchBlocks plan_batch(const std::vector<DomainSize>& dom, int es, int cus) {
   const BlockCost c = block_cost(es);
+  std::vector<int> of;
+  const std::vector<DomainClass> classes = domain_classes(dom, &of), samples = sample_classes(classes, 16);
+  double all_cells = 0.0;
+  for (const auto& q : classes) all_cells += q.count * q.cells();
   BatchBlocks best;
-  long long largest = 0, all_cells = 0;
-  for (const auto& d : dom) {
-    largest = std::max(largest, (long long)d.nx * d.ny);
-    all_cells += (long long)d.nx * d.ny;
-  }
-  const bool far = block_beyond_cache(es, all_cells);
   for (BlockShape s : kWholeShapes) {
-    if (largest > s.threads * s.cells) continue;
+    if (classes[0].cells() > s.threads * s.cells) continue;
     // no launch, no halo: the chain of a step, or the work of the busiest CU
     double work = 0.0;
-    for (const auto& d : dom) work += (c.density + c.collide) * ((d.nx * d.ny + 63) / 64);
+    for (const auto& q : classes) work += q.count * (c.density + c.collide) * ((q.size.nx * q.size.ny + 63) / 64);
     const double q = (double)((dom.size() + cus - 1) / cus);
     const double own = q * work / dom.size(), wait = c.step * std::ceil(q * s.threads / 512);
     best.us_per_step = std::sqrt(own * own + wait * wait);
@@ -207,46 +324,22 @@ inline BatchBlocks plan_batch(const std::vector<DomainSize>& dom, int es, int cu
     best.shape = s;
     break;
   }
-  // the division of a domain of least work; the caller's sums over its blocks
-  struct Cut {
-    int ntx = 0, nty = 0;
-    double work = 1e300, cells = 0.0;
-  };
-  auto cut = [&](const DomainSize& d, BlockShape s, int k, int finer) {
-    const int halo = 2 * (2 * k - 1);
-    Cut best_cut;
-    for_block_widths(d.nx, [&](int ntx) {
-      const int fewest = block_rows(d.nx, d.ny, ntx, k, s.threads * s.cells);
-      if (fewest == 0) return;
-      const int nty = std::min(d.ny, fewest * finer);
-      const int w = (d.nx + ntx - 1) / ntx, h = (d.ny + nty - 1) / nty;
-      const Cut q{ntx, nty, ntx * nty * block_work(c, w + halo, h + halo, k),
-                  (double)ntx * nty * ((double)(w + halo) * (h + halo) + (double)w * h)};
-      if (q.work + c.hide * c.moved * q.cells < best_cut.work + c.hide * c.moved * best_cut.cells) best_cut = q;
-    });
-    return best_cut;
-  };
-  // steps and shape from at most 16 domains spread over the batch, then every
-  // domain's division; a batch of fewer blocks than CUs divides them further
-  const size_t stride = (dom.size() + 15) / 16;
+  // a batch of fewer blocks than CUs divides its domains further
+  const bool far = block_beyond_cache(es, (long long)all_cells);
   int finer = 1;
   for (BlockShape s : kBlockShapes) {
     if (!block_shape_built(es, s) || (far && block_resident(es, s) < 2)) continue;
     for (int k = far ? 3 : kBlockMinSteps; k <= kBlockMaxSteps; ++k)
       for (int f = 1; f > 0;) {
-        double tiles = 0.0, work = 0.0, cells = 0.0;
-        size_t seen = 0;
-        for (size_t d = 0; d < dom.size(); d += stride, ++seen) {
-          const Cut q = cut(dom[d], s, k, f);
-          if (q.ntx == 0) break;
-          tiles += (double)q.ntx * q.nty;
-          work += q.work;
-          cells += q.cells;
+        BatchLaunchCost sums{es, k, block_resident(es, s)};
+        bool fits = true;
+        for (const auto& d : samples) {
+          const BlockCut q = cut_domain(c, d.size, s, k, f);
+          if (!(fits = q.ntx > 0)) break;
+          sums.add(q, d.count);
         }
-        if (seen < (dom.size() + stride - 1) / stride) break;
-        const double all = tiles * dom.size() / seen;
-        const double t = block_launch_time(c, k, std::ceil(all / cus), work / tiles, cells / tiles,
-                                           block_resident(es, s)) / k;
+        if (!fits) break;
+        const double t = sums.us(all_cells, cus) / k;
         if (t < best.us_per_step) {
           best = BatchBlocks{};
           best.k = k;
@@ -254,17 +347,23 @@ inline BatchBlocks plan_batch(const std::vector<DomainSize>& dom, int es, int cu
           best.us_per_step = t;
           finer = f;
         }
-        f = f == 1 && all * 2 <= cus ? (int)(cus / all) : 0;
+        f = f == 1 && sums.blocks * 2 <= cus ? (int)(cus / sums.blocks) : 0;
       }
   }
-  if (!best.whole)
-    for (size_t d = 0; d < dom.size(); ++d) {
-      const bool again = d > 0 && dom[d].nx == dom[d - 1].nx && dom[d].ny == dom[d - 1].ny;
-      const Cut q = again ? Cut{best.ntx.back(), best.nty.back()} : cut(dom[d], best.shape, best.k, finer);
-      if (q.ntx == 0) return BatchBlocks{};  // a domain that the chosen blocks do not fit: marching tiles
-      best.ntx.push_back(q.ntx);
-      best.nty.push_back(q.nty);
-    }
+  if (best.whole || best.k == 0) return best;
+  std::vector<BlockCut> cuts;
+  for (const auto& d : classes) {
+    cuts.push_back(cut_domain(c, d.size, best.shape, best.k, finer));
+    if (cuts.back().ntx == 0) return BatchBlocks{};  // a domain that the chosen blocks do not fit: marching tiles
+  }
+  BatchLaunchCost sums{es, best.k, block_resident(es, best.shape)};
+  for (size_t q = 0; q < classes.size(); ++q) sums.add(cuts[q], classes[q].count);
+  best.us_per_step = sums.us(all_cells, cus) / best.k;
+  best.tiles_us_per_step = batch_tiles_time(classes, es) / 2;
+  for (int q : of) {
+    best.ntx.push_back(cuts[q].ntx);
+    best.nty.push_back(cuts[q].nty);
+  }
   return best;
 }
 

@@ -1,0 +1,19 @@
+"""Block plans of batches of mixed sizes (lbm_plan.h): the choice of steps and shape, which the
+cover and capacity checks of test_block_launch.py leave open."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+from test_persistent_protocol import CSRC, PROTO, ROOT
+
+
+def test_plans_of_mixed_batches_see_every_domain(tmp_path):
+    exe, rocm = str(tmp_path / "plans"), "/opt/rocm/include"
+    if not os.path.isdir(rocm) or shutil.which("g++") is None:
+        pytest.skip("no HIP headers or g++")
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", rocm, "-I",
+                           os.path.join(ROOT, "include"), "-I", CSRC, "-o", exe, os.path.join(PROTO, "batch_plan.cpp")])
+    res = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0 and "0 failures" in res.stdout, res.stdout + res.stderr
