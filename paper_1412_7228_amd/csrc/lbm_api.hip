@@ -1338,13 +1338,10 @@ lbm_status batch_reduction(lbm_batch* b) {
   if (!b->d_obs) {
     const size_t ob = obs_domain_bytes();
     std::vector<unsigned char> h(ob * b->n);
-    long long rows = 0;
-    for (int d = 0; d < b->n; ++d) rows += b->g[d].ny;
     b->obs_most = 1;
     for (int d = 0; d < b->n; ++d)
       b->obs_most = std::max(b->obs_most, obs_fill_domain(b->g[d], b->m[d], static_cast<char*>(b->arena) + b->off[0][d],
-                                                          static_cast<char*>(b->arena) + b->off[1][d], rows,
-                                                          h.data() + d * ob));
+                                                          static_cast<char*>(b->arena) + b->off[1][d], h.data() + d * ob));
     void* q = nullptr;
     HIP_TRY(hipMalloc(&q, h.size()));
     hipError_t e = hipMemcpyAsync(q, h.data(), h.size(), hipMemcpyHostToDevice, b->stream);

@@ -96,12 +96,11 @@ int obs_partials_count(const Geometry& g);
 hipError_t launch_observables(lbm_precision prec, const Geometry& g, const ModelConsts& m, const void* f,
                               double* partials, double* red, hipStream_t s);
 // The observables of every domain of a batch: records of obs_domain_bytes()
-// filled on the host (obs_fill_domain returns the partials a domain takes, for
-// a batch of batch_rows rows in all) and copied to the device; `most` is the
+// filled on the host (obs_fill_domain returns the partials a domain takes) and
+// copied to the device; `most` is the
 // largest count, partials holds n * most * kNumRed doubles and red n * kNumObs.
 size_t obs_domain_bytes();
-int obs_fill_domain(const Geometry& g, const ModelConsts& m, const void* fa, const void* fb, long long batch_rows,
-                    void* out);
+int obs_fill_domain(const Geometry& g, const ModelConsts& m, const void* fa, const void* fb, void* out);
 hipError_t launch_batch_observables(lbm_precision prec, int eos, const void* domains, int n, int most, int parity,
                                     double* partials, double* red, hipStream_t s);
 // The device address of the file-scope scratch array of the current device
