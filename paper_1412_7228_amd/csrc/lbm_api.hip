@@ -10,6 +10,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -1077,9 +1078,8 @@ struct lbm_batch {
   // (records of the domains, partial sums, results in pinned host memory; likewise)
   double* work = nullptr;
   double* stage = nullptr;  // 3 fields of the largest domain (see kStageCells)
-  void* d_obs = nullptr;
-  int obs_most = 0;  // partials of the domain with the most
-  double* partials = nullptr;
+  void* d_obs = nullptr;  // the arrays of `obs` on the device
+  ObsBatch obs{};
   double* red = nullptr;
 };
 
@@ -1336,24 +1336,32 @@ lbm_status batch_scratch(lbm_batch* b) {
 // (after a failed allocation the others stay, and the next call completes it).
 lbm_status batch_reduction(lbm_batch* b) {
   if (!b->d_obs) {
-    const size_t ob = obs_domain_bytes();
-    std::vector<unsigned char> h(ob * b->n);
-    b->obs_most = 1;
-    for (int d = 0; d < b->n; ++d)
-      b->obs_most = std::max(b->obs_most, obs_fill_domain(b->g[d], b->m[d], static_cast<char*>(b->arena) + b->off[0][d],
-                                                          static_cast<char*>(b->arena) + b->off[1][d], h.data() + d * ob));
-    void* q = nullptr;
-    HIP_TRY(hipMalloc(&q, h.size()));
-    hipError_t e = hipMemcpyAsync(q, h.data(), h.size(), hipMemcpyHostToDevice, b->stream);
+    const size_t db = obs_domain_bytes(), lb = obs_block_bytes();
+    long long parts = 0;
+    for (int d = 0; d < b->n; ++d) parts += obs_partials_count(b->g[d]);
+    auto whole = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
+    const size_t list_at = whole(db * b->n), partials_at = list_at + whole(lb * parts);
+    std::unique_ptr<unsigned char[]> h(new (std::nothrow) unsigned char[partials_at]);
+    if (!h) return fail(LBM_ENOMEM, "host allocation failed");
+    long long at = 0;
+    for (int d = 0; d < b->n; ++d) {
+      obs_fill_domain(b->g[d], b->m[d], static_cast<char*>(b->arena) + b->off[0][d],
+                      static_cast<char*>(b->arena) + b->off[1][d], at, h.get() + d * db);
+      for (int k = 0; k < obs_partials_count(b->g[d]); ++k) obs_fill_block(d, k, h.get() + list_at + at++ * lb);
+    }
+    char* q = nullptr;
+    HIP_TRY(hipMalloc((void**)&q, partials_at + (size_t)parts * kNumRed * sizeof(double)));
+    hipError_t e = hipMemcpyAsync(q, h.get(), partials_at, hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) {
       (void)hipFree(q);
       HIP_TRY(e);
     }
     b->d_obs = q;
+    b->obs = ObsBatch{q, q + list_at, reinterpret_cast<double*>(q + partials_at), nullptr, b->n, parts};
   }
-  if (!b->partials) HIP_TRY(hipMalloc(&b->partials, (size_t)b->n * b->obs_most * kNumRed * sizeof(double)));
   if (!b->red) HIP_TRY(hipHostMalloc((void**)&b->red, (size_t)b->n * kNumObs * sizeof(double)));
+  b->obs.red = b->red;
   return LBM_OK;
 }
 
@@ -1450,7 +1458,7 @@ void lbm_batch_destroy(lbm_batch* b) {
   if (!b) return;
   (void)hipStreamSynchronize(b->stream);
   batch_free_layout(b);
-  for (void* q : {b->arena, (void*)b->d_head, (void*)b->d_done, (void*)b->d_err, (void*)b->work, b->d_obs, (void*)b->partials})
+  for (void* q : {b->arena, (void*)b->d_head, (void*)b->d_done, (void*)b->d_err, (void*)b->work, b->d_obs})
     if (q) (void)hipFree(q);
   for (double* q : {b->red, b->stage})
     if (q) (void)hipHostFree(q);
@@ -1565,8 +1573,7 @@ lbm_status lbm_batch_observables(lbm_batch* b, lbm_obs* out) {
   lbm_status st = batch_check_error(b);
   if (st != LBM_OK) return st;
   if ((st = batch_reduction(b)) != LBM_OK) return st;
-  HIP_TRY(launch_batch_observables(b->prec, b->eos, b->d_obs, b->n, b->obs_most, b->parity, b->partials, b->red,
-                                   b->stream));
+  HIP_TRY(launch_batch_observables(b->prec, b->eos, b->obs, b->parity, b->stream));
   HIP_TRY(hipStreamSynchronize(b->stream));
   lbm_status worst = LBM_OK;
   for (int d = 0; d < b->n; ++d) {

@@ -328,8 +328,10 @@ __global__ void __launch_bounds__(kRedThreads)
   obs_finish(f, geo, partials, nparts, red);
 }
 
-// A batch: grid (blocks of the largest domain, domains); a domain with fewer
-// tiles leaves its further blocks empty.  A domain has the tiles of the same
+// A batch: one workgroup per partial of every domain, from a list, so that the
+// workspace and the launch grow with the sum over the domains (one 4096^2 among
+// 10,000 of 64^2: 17 MB; records for n times the largest would take 1.1 GB and 18
+// million workgroups).  A domain has the tiles of the same
 // lattice alone, so its observables are those of the lattice bit for bit and do
 // not depend on what else is in the batch.  (Tiles of 16 rows where the batch is
 // large read fewer rows twice, a call over 256 domains of 64^2 to 512^2 340 us
@@ -339,24 +341,31 @@ struct ObsDomain {
   DevC<double> c;
   const void* f[2];
   ObsTiles t;
+  long long first;  // its partials in the batch's: first .. first + parts
+  int parts;
+};
+
+struct ObsBlock {
+  int domain, part;
 };
 
 template <typename T, int EOS>
 __global__ void __launch_bounds__(kRedThreads)
-    k_batch_obs(const ObsDomain* __restrict__ dom, int parity, double* __restrict__ partials) {
-  const ObsDomain& D = dom[blockIdx.y];
-  if ((int)blockIdx.x >= D.t.tiles) return;
-  obs_block<T, EOS, false>(static_cast<const T*>(D.f[parity]), D.g, D.c, D.t, blockIdx.x, gridDim.x,
-                    partials + ((long long)blockIdx.y * gridDim.x + blockIdx.x) * kNumRed);
+    k_batch_obs(const ObsDomain* __restrict__ dom, const ObsBlock* __restrict__ list, int parity,
+                double* __restrict__ partials) {
+  const ObsBlock b = list[blockIdx.x];
+  const ObsDomain& D = dom[b.domain];
+  obs_block<T, EOS, false>(static_cast<const T*>(D.f[parity]), D.g, D.c, D.t, b.part, D.parts,
+                           partials + (D.first + b.part) * kNumRed);
 }
 
 template <typename T>
 __global__ void __launch_bounds__(kRedThreads)
-    k_batch_obs_finish(const ObsDomain* __restrict__ dom, int parity, const double* __restrict__ partials, int most,
+    k_batch_obs_finish(const ObsDomain* __restrict__ dom, int parity, const double* __restrict__ partials,
                        double* __restrict__ red) {
   const ObsDomain& D = dom[blockIdx.x];
-  obs_finish(static_cast<const T*>(D.f[parity]), D.g, partials + (long long)blockIdx.x * most * kNumRed,
-             min(D.t.tiles, most), red + (long long)blockIdx.x * kNumObs);
+  obs_finish(static_cast<const T*>(D.f[parity]), D.g, partials + D.first * kNumRed, D.parts,
+             red + (long long)blockIdx.x * kNumObs);
 }
 
 template <typename T>
@@ -496,38 +505,46 @@ hipError_t launch_observables(lbm_precision prec, const Geometry& g, const Model
 
 size_t obs_domain_bytes() { return sizeof(ObsDomain); }
 
-int obs_fill_domain(const Geometry& g, const ModelConsts& m, const void* fa, const void* fb, void* out) {
-  *static_cast<ObsDomain*>(out) = ObsDomain{g, make_devc<double>(m), {fa, fb}, obs_tiles(g)};
-  return obs_partials_count(g);
+size_t obs_block_bytes() { return sizeof(ObsBlock); }
+
+void obs_fill_domain(const Geometry& g, const ModelConsts& m, const void* fa, const void* fb, long long first,
+                     void* out) {
+  *static_cast<ObsDomain*>(out) =
+      ObsDomain{g, make_devc<double>(m), {fa, fb}, obs_tiles(g), first, obs_partials_count(g)};
 }
 
+void obs_fill_block(int domain, int part, void* out) { *static_cast<ObsBlock*>(out) = ObsBlock{domain, part}; }
+
 template <typename T>
-static hipError_t batch_observables_t(int eos, const void* dv, int n, int most, int parity, double* partials,
-                                      double* red, hipStream_t s) {
+static hipError_t batch_observables_t(int eos, const ObsBatch& q, int parity, hipStream_t s) {
+  constexpr long long kMost = 1ll << 22;  // workgroups of a launch: its lanes are counted in 32 bits
+  const ObsDomain* d = static_cast<const ObsDomain*>(q.domains);
   const dim3 block(kRedThreads);
-  for (int first = 0; first < n; first += 32768) {  // a grid's y extent ends at 65,535
-    const ObsDomain* d = static_cast<const ObsDomain*>(dv) + first;
-    double* part = partials + (long long)first * most * kNumRed;
-    const dim3 grid(most, n - first < 32768 ? n - first : 32768);
+  for (long long first = 0; first < q.parts; first += kMost) {
+    const ObsBlock* l = static_cast<const ObsBlock*>(q.list) + first;
+    const dim3 grid((unsigned)(q.parts - first < kMost ? q.parts - first : kMost));
     switch (eos) {
-      case LBM_EOS_IDEAL: hipLaunchKernelGGL((k_batch_obs<T, LBM_EOS_IDEAL>), grid, block, 0, s, d, parity, part); break;
-      case LBM_EOS_CS: hipLaunchKernelGGL((k_batch_obs<T, LBM_EOS_CS>), grid, block, 0, s, d, parity, part); break;
-      case LBM_EOS_VDW: hipLaunchKernelGGL((k_batch_obs<T, LBM_EOS_VDW>), grid, block, 0, s, d, parity, part); break;
-      case LBM_EOS_PR: hipLaunchKernelGGL((k_batch_obs<T, LBM_EOS_PR>), grid, block, 0, s, d, parity, part); break;
+      case LBM_EOS_IDEAL: hipLaunchKernelGGL((k_batch_obs<T, LBM_EOS_IDEAL>), grid, block, 0, s, d, l, parity, q.partials); break;
+      case LBM_EOS_CS: hipLaunchKernelGGL((k_batch_obs<T, LBM_EOS_CS>), grid, block, 0, s, d, l, parity, q.partials); break;
+      case LBM_EOS_VDW: hipLaunchKernelGGL((k_batch_obs<T, LBM_EOS_VDW>), grid, block, 0, s, d, l, parity, q.partials); break;
+      case LBM_EOS_PR: hipLaunchKernelGGL((k_batch_obs<T, LBM_EOS_PR>), grid, block, 0, s, d, l, parity, q.partials); break;
       default: return hipErrorInvalidValue;
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_batch_obs_finish<T>, dim3(n), block, 0, s, static_cast<const ObsDomain*>(dv), parity, partials,
-                     most, red);
-  return hipGetLastError();
+  for (long long first = 0; first < q.n; first += kMost) {
+    const dim3 grid((unsigned)(q.n - first < kMost ? q.n - first : kMost));
+    hipLaunchKernelGGL(k_batch_obs_finish<T>, grid, block, 0, s, d + first, parity, q.partials, q.red + first * kNumObs);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
-hipError_t launch_batch_observables(lbm_precision prec, int eos, const void* domains, int n, int most, int parity,
-                                    double* partials, double* red, hipStream_t s) {
-  if (prec == LBM_FP32) return batch_observables_t<float>(eos, domains, n, most, parity, partials, red, s);
-  return batch_observables_t<double>(eos, domains, n, most, parity, partials, red, s);
+hipError_t launch_batch_observables(lbm_precision prec, int eos, const ObsBatch& q, int parity, hipStream_t s) {
+  if (prec == LBM_FP32) return batch_observables_t<float>(eos, q, parity, s);
+  return batch_observables_t<double>(eos, q, parity, s);
 }
 
 // ---------------------------------------------------------------------------

@@ -95,14 +95,23 @@ constexpr int kNumObs = kNumRed + 2;
 int obs_partials_count(const Geometry& g);
 hipError_t launch_observables(lbm_precision prec, const Geometry& g, const ModelConsts& m, const void* f,
                               double* partials, double* red, hipStream_t s);
-// The observables of every domain of a batch: records of obs_domain_bytes()
-// filled on the host (obs_fill_domain returns the partials a domain takes) and
-// copied to the device; `most` is the
-// largest count, partials holds n * most * kNumRed doubles and red n * kNumObs.
+// The observables of every domain of a batch: records of obs_domain_bytes() and
+// a list of its partials (obs_block_bytes() each), filled on the host and copied to
+// the device.  Domain d has obs_partials_count(g) partials, after those of the
+// domains before it.
+struct ObsBatch {
+  const void* domains;
+  const void* list;
+  double* partials;  // parts * kNumRed
+  double* red;       // n * kNumObs
+  long long n, parts;
+};
 size_t obs_domain_bytes();
-int obs_fill_domain(const Geometry& g, const ModelConsts& m, const void* fa, const void* fb, void* out);
-hipError_t launch_batch_observables(lbm_precision prec, int eos, const void* domains, int n, int most, int parity,
-                                    double* partials, double* red, hipStream_t s);
+size_t obs_block_bytes();
+void obs_fill_domain(const Geometry& g, const ModelConsts& m, const void* fa, const void* fb, long long first,
+                     void* out);
+void obs_fill_block(int domain, int part, void* out);
+hipError_t launch_batch_observables(lbm_precision prec, int eos, const ObsBatch& q, int parity, hipStream_t s);
 // The device address of the file-scope scratch array of the current device
 // (the partials of any lattice, then kNumObs doubles), resolved once per
 // device; and the largest lattice (cells) that the calls on it take.

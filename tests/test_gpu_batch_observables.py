@@ -44,3 +44,25 @@ def test_a_domains_observables_are_the_lattices(lbm, precision, copies):
     for i, o in enumerate(b.observables()):
         w = want[i % len(sizes)]
         assert all(o[k] == w[k] or (np.isnan(o[k]) and np.isnan(w[k])) for k in w), (i, o, w)
+
+
+def test_workspace_of_one_large_domain_among_many_small(lbm):
+    """One 2048^2 among 3,000 of 16^2: 2 MB of records, list and partials (n times the large domain's
+    partials would take 220 MB), within 64 MB with what the runtime rounds up; and the right values."""
+    import torch
+
+    print("[gpu-case] batch observables workspace, 3000 x 16^2 + 2048^2", flush=True)
+    sizes = [(16, 16)] * 3000 + [(2048, 2048)]
+    b = lbm.Batch([dict(nx=x, ny=y, eos="ideal", precision="fp32") for x, y in sizes])
+    g = np.random.default_rng(1)
+    small, large = 1.0 + 0.1 * g.random((16, 16)), 1.0 + 0.1 * g.random((2048, 2048))
+    for i in range(3000):
+        b.init_field(i, small)
+    b.init_field(3000, large)
+    b.sync()
+    free = torch.cuda.mem_get_info()[0]
+    obs = b.observables()
+    assert free - torch.cuda.mem_get_info()[0] < 64 << 20
+    for o, rho in ((obs[0], small), (obs[2999], small), (obs[3000], large)):
+        assert abs(o["mass"] - rho.sum()) <= rho.size * 2.0 ** -23 * 1.1  # nine FP32 populations a cell
+        assert abs(o["rho_max"] - rho.max()) <= 9 * 2.0 ** -24 * rho.max()
