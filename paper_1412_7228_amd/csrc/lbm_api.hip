@@ -337,11 +337,12 @@ struct lbm_ctx {
     int launches, parity, version;
   } graphs[4];
   int ngraphs, version;  // version: bumped whenever the launch geometry changes
-  // FP64 scratch for fields and observables (allocated on first use)
-  double* work;      // 4 * nx*ny: rho, U, psi, out
-  double* stage;     // small lattices: 3 * nx*ny of pinned host memory (see kStageCells)
+  // FP64 scratch for fields and observables, allocated with the first state
+  double* work;      // device: 4 * nx*ny (rho, U, psi, out), then the partials
   double* partials;  // obs_partials_count * kNumRed
-  double* red;       // kNumObs, in pinned host memory that the reduction writes
+  double* pinned;    // host memory that the kernels read and write: the stage, then red
+  double* stage;     // small lattices: 3 * nx*ny (see kStageCells)
+  double* red;       // kNumObs
 };
 
 namespace {
@@ -482,21 +483,23 @@ BlockPlan rows_block(lbm_ctx* c, int rows) {
 // as fast.
 constexpr size_t kStageCells = 1u << 18;
 
-lbm_status ensure_stage(double** stage, size_t cells) {
-  if (!*stage && cells <= kStageCells) HIP_TRY(hipHostMalloc((void**)stage, 3 * cells * sizeof(double)));
-  return LBM_OK;
-}
+// Doubles of pinned memory that stage fields of up to `cells` cells.
+size_t stage_doubles(size_t cells) { return cells <= kStageCells ? 3 * cells : 0; }
 
-// Allocates the scratch of the fields (kept on failure of a later one).
+// Allocates the scratch of the fields and the observables, so that no later call
+// does: one device allocation and one of pinned memory (each costs an allocation and a
+// release of 13 us; whatever is missing after a failure, the next call makes).
 lbm_status ensure_scratch(lbm_ctx* c) {
   const size_t n = (size_t)c->p.nx * c->p.ny;
-  if (!c->work) HIP_TRY(hipMalloc(&c->work, 4 * n * sizeof(double)));
-  return LBM_OK;
-}
-
-lbm_status ensure_reduction(lbm_ctx* c) {
-  if (!c->partials) HIP_TRY(hipMalloc(&c->partials, (size_t)obs_partials_count(c->g) * kNumRed * sizeof(double)));
-  if (!c->red) HIP_TRY(hipHostMalloc((void**)&c->red, kNumObs * sizeof(double)));
+  if (!c->work) {
+    HIP_TRY(hipMalloc((void**)&c->work, (4 * n + (size_t)obs_partials_count(c->g) * kNumRed) * sizeof(double)));
+    c->partials = c->work + 4 * n;
+  }
+  if (!c->pinned) {
+    HIP_TRY(hipHostMalloc((void**)&c->pinned, (stage_doubles(n) + kNumObs) * sizeof(double)));
+    c->stage = stage_doubles(n) ? c->pinned : nullptr;
+    c->red = c->pinned + stage_doubles(n);
+  }
   return LBM_OK;
 }
 
@@ -597,12 +600,6 @@ lbm_status observe(const lbm_ctx* c, double* partials, double* red, bool on_devi
   HIP_TRY(hipStreamSynchronize(c->stream));
   if (!on_device) std::memcpy(h, red, sizeof h);
   return finish_observables(c->p, c->m, h, c->step, o);
-}
-
-// Whether a field's read-out goes through the device scratch `work`: always for
-// the velocities (U and psi of the neighbours), otherwise without a stage.
-bool field_needs_work(int32_t which, const double* stage) {
-  return which == LBM_FIELD_UX || which == LBM_FIELD_UY || !stage;
 }
 
 lbm_status check_field(int32_t which) {
@@ -776,9 +773,7 @@ void lbm_destroy(lbm_ctx* c) {
     for (int i = 0; i < 2; ++i)
       if (c->buf[i]) (void)hipFree(c->buf[i]);
   if (c->work) (void)hipFree(c->work);
-  if (c->stage) (void)hipHostFree(c->stage);
-  if (c->partials) (void)hipFree(c->partials);
-  if (c->red) (void)hipHostFree(c->red);
+  if (c->pinned) (void)hipHostFree(c->pinned);
   if (c->own_stream) (void)hipStreamDestroy(c->stream);
   for (int i = 0; i < c->ngraphs; ++i) (void)hipGraphExecDestroy(c->graphs[i].exec);
   if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
@@ -836,8 +831,7 @@ lbm_status lbm_init_field(lbm_ctx* c, const double* rho, const double* ux, const
   const size_t n = (size_t)c->p.nx * c->p.ny;
   lbm_status st = check_density(rho, n);
   if (st != LBM_OK) return st;
-  if ((st = ensure_stage(&c->stage, n)) != LBM_OK) return st;
-  if (!c->stage && (st = ensure_scratch(c)) != LBM_OK) return st;
+  if ((st = ensure_scratch(c)) != LBM_OK) return st;
   c->cur = 0;
   if ((st = write_initial(c->p, c->g, rho, ux, uy, c->work, c->stage, c->buf[0], c->stream)) != LBM_OK) return st;
   c->step = 0;
@@ -929,7 +923,7 @@ lbm_status lbm_step_rows(lbm_ctx* c, int32_t n, int32_t y_begin, int32_t rows, i
 lbm_status lbm_observables(lbm_ctx* c, lbm_obs* o) {
   if (!c || !o) return fail(LBM_EINVAL, "NULL argument");
   if (!c->initialized) return fail(LBM_ESTATE, "observables before lbm_init_field");
-  lbm_status st = ensure_reduction(c);
+  lbm_status st = ensure_scratch(c);
   if (st != LBM_OK) return st;
   return observe(c, c->partials, c->red, false, o);
 }
@@ -956,8 +950,7 @@ lbm_status lbm_get_field(lbm_ctx* c, int32_t which, double* out) {
   if (!c->initialized) return fail(LBM_ESTATE, "field before lbm_init_field");
   lbm_status st = check_field(which);
   if (st != LBM_OK) return st;
-  if ((st = ensure_stage(&c->stage, (size_t)c->p.nx * c->p.ny)) != LBM_OK) return st;
-  if (field_needs_work(which, c->stage) && (st = ensure_scratch(c)) != LBM_OK) return st;
+  if ((st = ensure_scratch(c)) != LBM_OK) return st;
   return read_field(c->p, c->m, c->g, c->buf[c->cur], which, c->work, c->stage, c->stream, out);
 }
 
@@ -1074,13 +1067,12 @@ struct lbm_batch {
   // graph cache
   hipGraphExec_t exec = nullptr;
   int exec_mode = -1, exec_steps = 0, exec_parity = -1, exec_fuse = 0;
-  // FP64 scratch of fields (allocated on first use), and of the observables
-  // (records of the domains, partial sums, results in pinned host memory; likewise)
-  double* work = nullptr;
-  double* stage = nullptr;  // 3 fields of the largest domain (see kStageCells)
-  void* d_obs = nullptr;  // the arrays of `obs` on the device
+  // FP64 scratch of the fields and the observables, allocated with the first state
+  double* work = nullptr;   // device: 4 fields of the largest domain, then the arrays of `obs`
   ObsBatch obs{};
-  double* red = nullptr;
+  double* pinned = nullptr;  // host memory that the kernels read and write: the stage, then red
+  double* stage = nullptr;   // 3 fields of the largest domain (see kStageCells)
+  double* red = nullptr;     // n * kNumObs
 };
 
 namespace {
@@ -1327,15 +1319,10 @@ size_t batch_largest(const lbm_batch* b) {
   return cells;
 }
 
+// As ensure_scratch, with the records, list and partial sums of the observables.
 lbm_status batch_scratch(lbm_batch* b) {
-  if (!b->work) HIP_TRY(hipMalloc(&b->work, 4 * batch_largest(b) * sizeof(double)));
-  return LBM_OK;
-}
-
-// Records, partial sums and results of the observables: whatever is missing
-// (after a failed allocation the others stay, and the next call completes it).
-lbm_status batch_reduction(lbm_batch* b) {
-  if (!b->d_obs) {
+  const size_t largest = batch_largest(b);
+  if (!b->work) {
     const size_t db = obs_domain_bytes(), lb = obs_block_bytes();
     long long parts = 0;
     for (int d = 0; d < b->n; ++d) parts += obs_partials_count(b->g[d]);
@@ -1349,18 +1336,24 @@ lbm_status batch_reduction(lbm_batch* b) {
                       static_cast<char*>(b->arena) + b->off[1][d], at, h.get() + d * db);
       for (int k = 0; k < obs_partials_count(b->g[d]); ++k) obs_fill_block(d, k, h.get() + list_at + at++ * lb);
     }
+    const size_t fields = whole(4 * largest * sizeof(double));
     char* q = nullptr;
-    HIP_TRY(hipMalloc((void**)&q, partials_at + (size_t)parts * kNumRed * sizeof(double)));
-    hipError_t e = hipMemcpyAsync(q, h.get(), partials_at, hipMemcpyHostToDevice, b->stream);
+    HIP_TRY(hipMalloc((void**)&q, fields + partials_at + (size_t)parts * kNumRed * sizeof(double)));
+    hipError_t e = hipMemcpyAsync(q + fields, h.get(), partials_at, hipMemcpyHostToDevice, b->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
     if (e != hipSuccess) {
       (void)hipFree(q);
       HIP_TRY(e);
     }
-    b->d_obs = q;
+    b->work = reinterpret_cast<double*>(q);
+    q += fields;
     b->obs = ObsBatch{q, q + list_at, reinterpret_cast<double*>(q + partials_at), nullptr, b->n, parts};
   }
-  if (!b->red) HIP_TRY(hipHostMalloc((void**)&b->red, (size_t)b->n * kNumObs * sizeof(double)));
+  if (!b->pinned) {
+    HIP_TRY(hipHostMalloc((void**)&b->pinned, (stage_doubles(largest) + (size_t)b->n * kNumObs) * sizeof(double)));
+    b->stage = stage_doubles(largest) ? b->pinned : nullptr;
+    b->red = b->pinned + stage_doubles(largest);
+  }
   b->obs.red = b->red;
   return LBM_OK;
 }
@@ -1458,10 +1451,9 @@ void lbm_batch_destroy(lbm_batch* b) {
   if (!b) return;
   (void)hipStreamSynchronize(b->stream);
   batch_free_layout(b);
-  for (void* q : {b->arena, (void*)b->d_head, (void*)b->d_done, (void*)b->d_err, (void*)b->work, b->d_obs})
+  for (void* q : {b->arena, (void*)b->d_head, (void*)b->d_done, (void*)b->d_err, (void*)b->work})
     if (q) (void)hipFree(q);
-  for (double* q : {b->red, b->stage})
-    if (q) (void)hipHostFree(q);
+  if (b->pinned) (void)hipHostFree(b->pinned);
   delete b;
 }
 
@@ -1520,8 +1512,7 @@ lbm_status lbm_batch_init_field(lbm_batch* b, int32_t i, const double* rho, cons
   const size_t n = (size_t)b->p[i].nx * b->p[i].ny;
   lbm_status st = check_density(rho, n);
   if (st != LBM_OK) return st;
-  if ((st = ensure_stage(&b->stage, batch_largest(b))) != LBM_OK) return st;
-  if (!b->stage && (st = batch_scratch(b)) != LBM_OK) return st;
+  if ((st = batch_scratch(b)) != LBM_OK) return st;
   HIP_TRY(hipStreamSynchronize(b->stream));
   void* f = static_cast<char*>(b->arena) + b->off[b->parity][i];
   if ((st = write_initial(b->p[i], b->g[i], rho, ux, uy, b->work, b->stage, f, b->stream)) != LBM_OK) return st;
@@ -1572,7 +1563,7 @@ lbm_status lbm_batch_observables(lbm_batch* b, lbm_obs* out) {
   if (!b || !out) return fail(LBM_EINVAL, "NULL argument");
   lbm_status st = batch_check_error(b);
   if (st != LBM_OK) return st;
-  if ((st = batch_reduction(b)) != LBM_OK) return st;
+  if ((st = batch_scratch(b)) != LBM_OK) return st;
   HIP_TRY(launch_batch_observables(b->prec, b->eos, b->obs, b->parity, b->stream));
   HIP_TRY(hipStreamSynchronize(b->stream));
   lbm_status worst = LBM_OK;
@@ -1590,8 +1581,7 @@ lbm_status lbm_batch_get_field(lbm_batch* b, int32_t i, int32_t which, double* o
   lbm_status st = batch_check_error(b);
   if (st != LBM_OK) return st;
   if ((st = check_field(which)) != LBM_OK) return st;
-  if ((st = ensure_stage(&b->stage, batch_largest(b))) != LBM_OK) return st;
-  if (field_needs_work(which, b->stage) && (st = batch_scratch(b)) != LBM_OK) return st;
+  if ((st = batch_scratch(b)) != LBM_OK) return st;
   const void* f = static_cast<char*>(b->arena) + b->off[b->parity][i];
   return read_field(b->p[i], b->m[i], b->g[i], f, which, b->work, b->stage, b->stream, out);
 }

@@ -1,0 +1,60 @@
+"""When the library allocates: its calls of hipMalloc and hipHostMalloc counted (in a process of
+their own, through a shim in the global scope)."""
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+PRELUDE = """
+import ctypes, json, os, sys
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+sys.path.insert(0, sys.argv[2])
+import numpy as np
+from paper_1412_7228_amd import inputs, lbm
+lbm.load_library()
+out = {}
+cfg = dict(eos="cs", T_over_Tc=0.8, A=-0.5, kappa=0.3)
+def counted(name, f):
+    before = shim.shim_mallocs(), shim.shim_pinned()
+    f()
+    out[name] = [shim.shim_mallocs() - before[0], shim.shim_pinned() - before[1]]
+"""
+
+
+def _run(tmp_path, body):
+    shim = str(tmp_path / "shim.so")
+    subprocess.check_call(["g++", "-O1", "-shared", "-fPIC", "-std=c++17", "-o", shim,
+                           os.path.join(HERE, "protocol", "hip_alloc_shim.cpp"), "-ldl"])
+    script = tmp_path / "script.py"
+    script.write_text(PRELUDE + body + "\nprint('RESULT ' + json.dumps(out))\n")
+    res = subprocess.run([sys.executable, "-u", str(script), shim, os.path.dirname(HERE)], capture_output=True, text=True,
+                         timeout=100)
+    assert res.returncode == 0, res.stdout + res.stderr
+    return json.loads(next(l for l in res.stdout.splitlines() if l.startswith("RESULT "))[7:])
+
+
+def test_nothing_is_allocated_after_the_state_is_set(tmp_path):
+    """Steps and every read-out of an initialised lattice or batch allocate nothing (a caller may
+    have taken all memory since, or forbid allocations); setting the state does."""
+    print("[gpu-case] allocations after init: 100^2, 600^2, a batch", flush=True)
+    r = _run(tmp_path, """
+for n in (100, 600):
+    lat = lbm.Lattice(dict(cfg, nx=n, ny=n))
+    counted(f"init {n}", lambda: lat.init_field(inputs.spinodal(n, n, 0.16, seed=1)))
+    counted(f"step {n}", lambda: (lat.step(7), lat.sync()))
+    counted(f"observables {n}", lambda: lat.observables(check=False))
+    counted(f"fields {n}", lambda: (lat.fields(), lat.field("f3")))
+b = lbm.Batch([dict(cfg, nx=n, ny=n) for n in (64, 100)])
+counted("init batch", lambda: [b.init_field(i, inputs.spinodal(n, n, 0.16, seed=1)) for i, n in enumerate((64, 100))])
+counted("step batch", lambda: (b.step(7), b.sync()))
+counted("observables batch", lambda: b.observables())
+counted("fields batch", lambda: (b.field(0, "rho"), b.field(1, "ux")))
+""")
+    assert all(v == [1, 1] for k, v in r.items() if k.startswith("init")), r
+    assert all(v == [0, 0] for k, v in r.items() if not k.startswith("init")), r
