@@ -338,11 +338,11 @@ struct lbm_ctx {
   } graphs[4];
   int ngraphs, version;  // version: bumped whenever the launch geometry changes
   // FP64 scratch for fields and observables, allocated with the first state
-  double* work;      // device: 4 * nx*ny (rho, U, psi, out), then the partials
+  double* work;      // device: 4 * nx*ny (rho, U, psi, out), then the partials and kNumObs
   double* partials;  // obs_partials_count * kNumRed
-  double* pinned;    // host memory that the kernels read and write: the stage, then red
+  double* pinned;    // host memory that the kernels read and write (may be null): the stage, then red
   double* stage;     // small lattices: 3 * nx*ny (see kStageCells)
-  double* red;       // kNumObs
+  double* red;       // kNumObs, in pinned memory or on the device
 };
 
 namespace {
@@ -483,20 +483,29 @@ BlockPlan rows_block(lbm_ctx* c, int rows) {
 // as fast.
 constexpr size_t kStageCells = 1u << 18;
 
+// Pinned host memory, or null where the system gives none: the callers then copy
+// from and to device arrays, as they do for fields too large to stage.
+void* pinned_memory(size_t bytes) {
+  void* q = nullptr;
+  if (hipHostMalloc(&q, bytes) == hipSuccess) return q;
+  (void)hipGetLastError();
+  return nullptr;
+}
+
 // Doubles of pinned memory that stage fields of up to `cells` cells.
 size_t stage_doubles(size_t cells) { return cells <= kStageCells ? 3 * cells : 0; }
 
 // Allocates the scratch of the fields and the observables, so that no later call
 // does: one device allocation and one of pinned memory (each costs an allocation and a
-// release of 13 us; whatever is missing after a failure, the next call makes).
+// release of 13 us).
 lbm_status ensure_scratch(lbm_ctx* c) {
-  const size_t n = (size_t)c->p.nx * c->p.ny;
-  if (!c->work) {
-    HIP_TRY(hipMalloc((void**)&c->work, (4 * n + (size_t)obs_partials_count(c->g) * kNumRed) * sizeof(double)));
-    c->partials = c->work + 4 * n;
-  }
-  if (!c->pinned) {
-    HIP_TRY(hipHostMalloc((void**)&c->pinned, (stage_doubles(n) + kNumObs) * sizeof(double)));
+  if (c->work) return LBM_OK;
+  const size_t n = (size_t)c->p.nx * c->p.ny, partials = (size_t)obs_partials_count(c->g) * kNumRed;
+  HIP_TRY(hipMalloc((void**)&c->work, (4 * n + partials + kNumObs) * sizeof(double)));
+  c->partials = c->work + 4 * n;
+  c->red = c->partials + partials;
+  c->pinned = static_cast<double*>(pinned_memory((stage_doubles(n) + kNumObs) * sizeof(double)));
+  if (c->pinned) {
     c->stage = stage_doubles(n) ? c->pinned : nullptr;
     c->red = c->pinned + stage_doubles(n);
   }
@@ -925,7 +934,7 @@ lbm_status lbm_observables(lbm_ctx* c, lbm_obs* o) {
   if (!c->initialized) return fail(LBM_ESTATE, "observables before lbm_init_field");
   lbm_status st = ensure_scratch(c);
   if (st != LBM_OK) return st;
-  return observe(c, c->partials, c->red, false, o);
+  return observe(c, c->partials, c->red, !c->pinned, o);
 }
 
 lbm_status lbm_observables_noalloc(lbm_ctx* c, lbm_obs* o) {
@@ -1068,11 +1077,10 @@ struct lbm_batch {
   hipGraphExec_t exec = nullptr;
   int exec_mode = -1, exec_steps = 0, exec_parity = -1, exec_fuse = 0;
   // FP64 scratch of the fields and the observables, allocated with the first state
-  double* work = nullptr;   // device: 4 fields of the largest domain, then the arrays of `obs`
+  double* work = nullptr;    // device: 4 fields of the largest domain, then the arrays of `obs`
   ObsBatch obs{};
-  double* pinned = nullptr;  // host memory that the kernels read and write: the stage, then red
+  double* pinned = nullptr;  // host memory that the kernels read and write (may be null): the stage, then obs.red
   double* stage = nullptr;   // 3 fields of the largest domain (see kStageCells)
-  double* red = nullptr;     // n * kNumObs
 };
 
 namespace {
@@ -1321,40 +1329,38 @@ size_t batch_largest(const lbm_batch* b) {
 
 // As ensure_scratch, with the records, list and partial sums of the observables.
 lbm_status batch_scratch(lbm_batch* b) {
-  const size_t largest = batch_largest(b);
-  if (!b->work) {
-    const size_t db = obs_domain_bytes(), lb = obs_block_bytes();
-    long long parts = 0;
-    for (int d = 0; d < b->n; ++d) parts += obs_partials_count(b->g[d]);
-    auto whole = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
-    const size_t list_at = whole(db * b->n), partials_at = list_at + whole(lb * parts);
-    std::unique_ptr<unsigned char[]> h(new (std::nothrow) unsigned char[partials_at]);
-    if (!h) return fail(LBM_ENOMEM, "host allocation failed");
-    long long at = 0;
-    for (int d = 0; d < b->n; ++d) {
-      obs_fill_domain(b->g[d], b->m[d], static_cast<char*>(b->arena) + b->off[0][d],
-                      static_cast<char*>(b->arena) + b->off[1][d], at, h.get() + d * db);
-      for (int k = 0; k < obs_partials_count(b->g[d]); ++k) obs_fill_block(d, k, h.get() + list_at + at++ * lb);
-    }
-    const size_t fields = whole(4 * largest * sizeof(double));
-    char* q = nullptr;
-    HIP_TRY(hipMalloc((void**)&q, fields + partials_at + (size_t)parts * kNumRed * sizeof(double)));
-    hipError_t e = hipMemcpyAsync(q + fields, h.get(), partials_at, hipMemcpyHostToDevice, b->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
-    if (e != hipSuccess) {
-      (void)hipFree(q);
-      HIP_TRY(e);
-    }
-    b->work = reinterpret_cast<double*>(q);
-    q += fields;
-    b->obs = ObsBatch{q, q + list_at, reinterpret_cast<double*>(q + partials_at), nullptr, b->n, parts};
+  if (b->work) return LBM_OK;
+  const size_t largest = batch_largest(b), db = obs_domain_bytes(), lb = obs_block_bytes();
+  long long parts = 0;
+  for (int d = 0; d < b->n; ++d) parts += obs_partials_count(b->g[d]);
+  auto whole = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
+  const size_t list_at = whole(db * b->n), partials_at = list_at + whole(lb * parts);
+  std::unique_ptr<unsigned char[]> h(new (std::nothrow) unsigned char[partials_at]);
+  if (!h) return fail(LBM_ENOMEM, "host allocation failed");
+  long long at = 0;
+  for (int d = 0; d < b->n; ++d) {
+    obs_fill_domain(b->g[d], b->m[d], static_cast<char*>(b->arena) + b->off[0][d],
+                    static_cast<char*>(b->arena) + b->off[1][d], at, h.get() + d * db);
+    for (int k = 0; k < obs_partials_count(b->g[d]); ++k) obs_fill_block(d, k, h.get() + list_at + at++ * lb);
   }
-  if (!b->pinned) {
-    HIP_TRY(hipHostMalloc((void**)&b->pinned, (stage_doubles(largest) + (size_t)b->n * kNumObs) * sizeof(double)));
+  const size_t fields = whole(4 * largest * sizeof(double)), red = (size_t)b->n * kNumObs;
+  char* q = nullptr;
+  HIP_TRY(hipMalloc((void**)&q, fields + partials_at + ((size_t)parts * kNumRed + red) * sizeof(double)));
+  hipError_t e = hipMemcpyAsync(q + fields, h.get(), partials_at, hipMemcpyHostToDevice, b->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
+  if (e != hipSuccess) {
+    (void)hipFree(q);
+    HIP_TRY(e);
+  }
+  b->work = reinterpret_cast<double*>(q);
+  q += fields;
+  double* partials = reinterpret_cast<double*>(q + partials_at);
+  b->obs = ObsBatch{q, q + list_at, partials, partials + parts * kNumRed, b->n, parts};
+  b->pinned = static_cast<double*>(pinned_memory((stage_doubles(largest) + red) * sizeof(double)));
+  if (b->pinned) {
     b->stage = stage_doubles(largest) ? b->pinned : nullptr;
-    b->red = b->pinned + stage_doubles(largest);
+    b->obs.red = b->pinned + stage_doubles(largest);
   }
-  b->obs.red = b->red;
   return LBM_OK;
 }
 
@@ -1565,10 +1571,18 @@ lbm_status lbm_batch_observables(lbm_batch* b, lbm_obs* out) {
   if (st != LBM_OK) return st;
   if ((st = batch_scratch(b)) != LBM_OK) return st;
   HIP_TRY(launch_batch_observables(b->prec, b->eos, b->obs, b->parity, b->stream));
+  const double* red = b->obs.red;
+  std::unique_ptr<double[]> copy;
+  if (!b->pinned) {
+    copy.reset(new (std::nothrow) double[(size_t)b->n * kNumObs]);
+    if (!copy) return fail(LBM_ENOMEM, "host allocation failed");
+    HIP_TRY(hipMemcpyAsync(copy.get(), red, (size_t)b->n * kNumObs * sizeof(double), hipMemcpyDeviceToHost, b->stream));
+    red = copy.get();
+  }
   HIP_TRY(hipStreamSynchronize(b->stream));
   lbm_status worst = LBM_OK;
   for (int d = 0; d < b->n; ++d) {
-    st = finish_observables(b->p[d], b->m[d], b->red + (size_t)d * kNumObs, b->step, &out[d]);
+    st = finish_observables(b->p[d], b->m[d], red + (size_t)d * kNumObs, b->step, &out[d]);
     if (st != LBM_OK && worst == LBM_OK) worst = st;
   }
   if (worst != LBM_OK) return fail(worst, "at least one batch domain holds non-finite densities or U > 0 cells");
@@ -1601,9 +1615,11 @@ struct lbm_mlp {
   float *xd = nullptr, *td = nullptr;  // the training set of lbm_mlp_set_data (never reused as scratch)
   // pinned host memory that the kernels read and write directly: the samples of
   // a forward or backward call of up to stage_rows, the parameters or gradients
+  // (null, and no rows, where the system gave none)
   float *stage_in = nullptr, *stage_out = nullptr, *stage_params = nullptr;
   int stage_rows = 0;
-  float* loss = nullptr;  // pinned too
+  float* loss = nullptr;  // pinned too, or on the device
+  bool loss_pinned = false;
   int loss_cap = 0;
   int ndata = 0;
   int64_t adam_t = 0;
@@ -1614,6 +1630,14 @@ namespace {
 // Samples of a call that pass through pinned memory; a larger call copies (2.4
 // MB and more, where the transfer is what counts).
 constexpr int kMlpStageRows = 1 << 16;
+
+hipError_t mlp_free_loss(lbm_mlp* m) {
+  float* old = m->loss;
+  m->loss = nullptr;  // forgotten before anything can fail, so no later call uses it
+  m->loss_cap = 0;
+  if (!old) return hipSuccess;
+  return m->loss_pinned ? hipHostFree(old) : hipFree(old);
+}
 
 lbm_status mlp_check_n(const lbm_mlp* m, int32_t n) {
   if (n < 1 || n > m->max_batch) return fail(LBM_EINVAL, "batch of %d samples outside [1, %d]", n, m->max_batch);
@@ -1652,11 +1676,14 @@ lbm_status lbm_mlp_create(int32_t max_batch, void* hip_stream, lbm_mlp** out) {
       *q.at = m->arena + off;
       off += whole(q.bytes);
     }
-    m->stage_rows = std::min(max_batch, kMlpStageRows);
-    const size_t staged = (size_t)m->stage_rows * 3;
-    e = hipHostMalloc((void**)&m->stage_in, (3 * staged + np) * sizeof(float));
-    m->stage_out = m->stage_in + 2 * staged;
-    m->stage_params = m->stage_out + staged;
+    const int rows = std::min(max_batch, kMlpStageRows);
+    const size_t staged = (size_t)rows * 3;
+    m->stage_in = static_cast<float*>(pinned_memory((3 * staged + np) * sizeof(float)));
+    if (m->stage_in) {
+      m->stage_rows = rows;
+      m->stage_out = m->stage_in + 2 * staged;
+      m->stage_params = m->stage_out + staged;
+    }
   }
   if (e == hipSuccess) e = hipMemsetAsync(m->w.master, 0, np * 4, m->stream);
   if (e == hipSuccess) e = hipMemsetAsync(m->m, 0, np * 4, m->stream);
@@ -1674,8 +1701,8 @@ void lbm_mlp_destroy(lbm_mlp* m) {
   if (!m) return;
   (void)hipStreamSynchronize(m->stream);
   if (m->arena) (void)hipFree(m->arena);
-  for (void* q : {(void*)m->stage_in, (void*)m->loss})
-    if (q) (void)hipHostFree(q);
+  if (m->stage_in) (void)hipHostFree(m->stage_in);
+  (void)mlp_free_loss(m);
   delete m;
 }
 
@@ -1693,9 +1720,13 @@ lbm_status lbm_mlp_set_params(lbm_mlp* m, const float* params) {
 
 lbm_status lbm_mlp_get_params(lbm_mlp* m, float* params) {
   if (!m || !params) return fail(LBM_EINVAL, "NULL argument");
-  HIP_TRY(launch_mlp_read(m->w.master, m->stage_params, m->stream));
+  const size_t bytes = (size_t)mlp_param_count() * sizeof(float);
+  if (m->stage_params)
+    HIP_TRY(launch_mlp_read(m->w.master, m->stage_params, m->stream));
+  else
+    HIP_TRY(hipMemcpyAsync(params, m->w.master, bytes, hipMemcpyDeviceToHost, m->stream));
   HIP_TRY(hipStreamSynchronize(m->stream));
-  std::memcpy(params, m->stage_params, (size_t)mlp_param_count() * sizeof(float));
+  if (m->stage_params) std::memcpy(params, m->stage_params, bytes);
   return LBM_OK;
 }
 
@@ -1762,12 +1793,10 @@ lbm_status lbm_mlp_train(lbm_mlp* m, int32_t iters, float lr, float* loss_out) {
   if (m->ndata < 1) return fail(LBM_ESTATE, "lbm_mlp_train before lbm_mlp_set_data");
   if (iters < 0 || !(lr > 0.f)) return fail(LBM_EINVAL, "iters must be >= 0 and lr > 0");
   if (iters > m->loss_cap) {
-    // forget the old buffer before anything can fail, so no later call uses it
-    float* old = m->loss;
-    m->loss = nullptr;
-    m->loss_cap = 0;
-    if (old) HIP_TRY(hipHostFree(old));
-    HIP_TRY(hipHostMalloc((void**)&m->loss, (size_t)iters * 4));
+    HIP_TRY(mlp_free_loss(m));
+    m->loss = static_cast<float*>(pinned_memory((size_t)iters * 4));
+    m->loss_pinned = m->loss != nullptr;
+    if (!m->loss) HIP_TRY(hipMalloc((void**)&m->loss, (size_t)iters * 4));
     m->loss_cap = iters;
   }
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
@@ -1778,8 +1807,11 @@ lbm_status lbm_mlp_train(lbm_mlp* m, int32_t iters, float lr, float* loss_out) {
     HIP_TRY(launch_mlp_update(m->acts, m->max_batch, m->w, m->m, m->v, lr, b1, b2, eps, c1, c2, m->y, m->td, m->ndata,
                               m->loss + it, m->stream));
   }
+  const bool out = loss_out && iters > 0;
+  if (out && !m->loss_pinned)
+    HIP_TRY(hipMemcpyAsync(loss_out, m->loss, (size_t)iters * 4, hipMemcpyDeviceToHost, m->stream));
   HIP_TRY(hipStreamSynchronize(m->stream));
-  if (loss_out && iters > 0) std::memcpy(loss_out, m->loss, (size_t)iters * 4);
+  if (out && m->loss_pinned) std::memcpy(loss_out, m->loss, (size_t)iters * 4);
   return LBM_OK;
 }
 

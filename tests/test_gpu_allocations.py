@@ -58,3 +58,37 @@ counted("fields batch", lambda: (b.field(0, "rho"), b.field(1, "ux")))
 """)
     assert all(v == [1, 1] for k, v in r.items() if k.startswith("init")), r
     assert all(v == [0, 0] for k, v in r.items() if not k.startswith("init")), r
+
+
+def test_refused_pinned_memory_falls_back_to_copies(tmp_path):
+    """Where the system gives no pinned memory, every call that uses it works through device arrays and
+    copies, with the same results bit for bit."""
+    print("[gpu-case] refused pinned memory: a lattice, a batch, the network", flush=True)
+    r = _run(tmp_path, """
+def results():
+    q = []
+    lat = lbm.Lattice(dict(cfg, nx=60, ny=50))
+    g = np.random.default_rng(0)
+    lat.init_field(inputs.spinodal(60, 50, 0.16, seed=1), 1e-3 * g.random((50, 60)), 1e-3 * g.random((50, 60)))
+    lat.step(9)
+    q += [lat.f_soa(), lat.fields()["rho"], lat.fields()["ux"], np.array(list(lat.observables(check=False).values()))]
+    b = lbm.Batch([dict(cfg, nx=n, ny=n) for n in (20, 60)])
+    for i, n in enumerate((20, 60)):
+        b.init_field(i, inputs.spinodal(n, n, 0.16, seed=1))
+    b.step(5)
+    q += [b.f_soa(1), b.field(0, "uy")] + [np.array(list(o.values())) for o in b.observables()]
+    net = lbm.MLP(max_batch=64)
+    net.set_params(g.normal(0, 0.1, net.nparams))
+    x, t = g.normal(size=(50, 3)), g.normal(size=(50, 3))
+    q += [net.forward(x), *net.backward(x, t)]
+    net.set_data(x, t)
+    q += [net.train(5, 1e-3), net.train(9, 1e-3), net.params()]
+    return q
+a = results()
+shim.shim_refuse_pinned(1)
+before = shim.shim_pinned()
+b = results()
+out["asked"] = shim.shim_pinned() - before
+out["same"] = [bool(np.array_equal(x, y, equal_nan=True)) for x, y in zip(a, b)]
+""")
+    assert r["asked"] >= 3 and all(r["same"]) and len(r["same"]) == 14, r
