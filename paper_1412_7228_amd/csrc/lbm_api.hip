@@ -316,6 +316,7 @@ struct lbm_ctx {
   int fuse;     // steps per pass: 1 or 2
   bool own_shape;   // the launch shape is the library's default, not the caller's
   BlockPlan block;  // block launches (lbm_block.hip) of lbm_step; k = 0: marching tiles
+  LatticeRest rest; // what ends a call in block launches
   struct RowPlan {
     int rows;
     BlockPlan plan;
@@ -458,6 +459,13 @@ BlockPlan default_block(const lbm_params& p) {
   return plan_lattice(p.nx, p.ny, es, device_cus(), kBlockMinSteps, kBlockMaxSteps, nullptr);
 }
 
+// Block launches of a context in the default shape, or the marching tiles alone.
+void set_block(lbm_ctx* c, bool own_shape) {
+  c->own_shape = own_shape;
+  c->block = own_shape ? default_block(c->p) : BlockPlan{};
+  c->rest = lattice_rest((int)elem_size(c->p), c->p.nx, c->p.ny, c->g.nstrips * c->g.tile_x, c->g2.nstrips * c->g2.tile_x);
+}
+
 // The block plan of a two-step launch over `rows` rows in the default shape
 // (k = 0: marching tiles), kept for the last four row counts.
 BlockPlan rows_block(lbm_ctx* c, int rows) {
@@ -529,8 +537,7 @@ lbm_status make_ctx(const lbm_params* p, void* stream, void* ba, void* bb, size_
   default_launch2(*p, &tx, &ty);
   set_geometry2(c, tx, ty);
   c->fuse = 2;
-  c->own_shape = true;
-  c->block = default_block(*p);
+  set_block(c, true);
   c->buf_bytes = state_elems(*p) * elem_size(*p);
   c->step = 0;
   c->cur = 0;
@@ -662,7 +669,8 @@ hipError_t launch_pass(const lbm_ctx* c, int steps, int cur, hipStream_t s) {
   const lbm_precision prec = (lbm_precision)c->p.precision;
   const void* from = c->buf[cur];
   void* to = c->buf[1 - cur];
-  if (c->block.k > 0) return launch_block(prec, c->g, c->m, c->block, steps, from, to, s);
+  const bool on_tiles = steps < c->block.k && ((steps == 1 && c->rest.one) || (steps == 2 && c->rest.two));
+  if (c->block.k > 0 && !on_tiles) return launch_block(prec, c->g, c->m, c->block, steps, from, to, s);
   if (steps == 2) return launch_step2(prec, c->g2, c->m, from, to, s);
   return launch_step(prec, c->g, c->m, from, to, s);
 }
@@ -820,8 +828,7 @@ lbm_status lbm_set_launch(lbm_ctx* c, const lbm_launch* l) {
   }
   c->fuse = fuse;
   // a shape asked for is the shape that runs; the defaults leave the choice open
-  c->own_shape = fuse == 2 && l->tile_x == 0 && l->tile_y == 0;
-  c->block = c->own_shape ? default_block(c->p) : BlockPlan{};
+  set_block(c, fuse == 2 && l->tile_x == 0 && l->tile_y == 0);
   ++c->version;  // cached graphs hold the old shape
   return LBM_OK;
 }
@@ -886,7 +893,7 @@ lbm_status lbm_step(lbm_ctx* c, int64_t n) {
     left -= (int64_t)per * kGraphLaunches;
   }
   while (left > 0) {
-    const int k = (int)std::min<int64_t>(left, per);
+    const int k = lattice_next_steps(left, per, c->rest);
     HIP_TRY(launch_pass(c, k, c->cur, c->stream));
     c->cur = 1 - c->cur;
     left -= k;

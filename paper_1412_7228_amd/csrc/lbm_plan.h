@@ -115,6 +115,32 @@ inline bool block_beyond_cache(int es, long long cells) { return es == 8 && cell
 // launches, 447 / 669 us.
 inline long long block_max_row_cells(int es) { return es == 4 ? 3ll << 19 : 1ll << 20; }
 
+// The end of a call on a lattice in blocks: fewer steps than a launch's k load and
+// store as much for less work, so one step, or two where k is three, may go to the
+// marching tiles: lattices above these sizes whose strips leave at most a fifth of
+// their lanes idle (lanes: of a row of strips).  Measured by blocks / by tiles, us a call
+// in a loop: one step, FP32 886^2 12.9 / 14.7, 1000^2 16.1 / 15.6, 2048^2 69.4 / 57.7,
+// 300 x 5000 (idle lanes) 22.1 / 22.9, FP64 1000^2 25.9 / 24.5, 1254^2 37.1 / 42.2, 1448^2
+// 68.5 / 65.8, 2048^2 132 / 118; two steps, FP32 1448^2 38.6 / 38.9, 1700^2 50.1 / 53.8,
+// 2048^2 85.6 / 78.0, 3000^2 179 / 159, FP64 1130^2 42.2 / 43.1, 1254^2 51.9 / 51.2, 1448^2
+// 84.6 / 78.8, 2048^2 165 / 145, 300 x 5000 48.2 / 62.2; four as three and one / as two
+// and two by tiles, FP32 2048^2 170 / 155, FP64 1130^2 89.4 / 86.4.
+struct LatticeRest {
+  bool one, two;  // by the tiles
+};
+
+inline LatticeRest lattice_rest(int es, int nx, int ny, int lanes1, int lanes2) {
+  const long long cells = (long long)nx * ny;
+  return {cells > (es == 4 ? 7ll << 17 : 31ll << 16) && 4ll * lanes1 <= 5ll * nx,
+          cells > (es == 4 ? 7ll << 19 : 1ll << 20) && 4ll * lanes2 <= 5ll * nx};
+}
+
+// Steps of the next launch of a call with `left` steps to go.
+inline int lattice_next_steps(long long left, int k, LatticeRest r) {
+  if (k == 3 && left == 4 && r.two) return 2;
+  return left < k ? (int)left : k;
+}
+
 // Widths tried for a block: every sixth of an octave, 3 to 512 columns.
 template <typename F>
 void for_block_widths(int nx, F f) {
