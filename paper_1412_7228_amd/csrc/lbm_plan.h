@@ -153,6 +153,15 @@ void for_block_widths(int nx, F f) {
   }
 }
 
+// A state whose two buffers pass the 256 MB last-level cache moves its cells at the
+// rate of HBM: a launch takes at least its loads and stores at 4.5 TB/s (FP32) or
+// 5.0 (FP64), the halos' second reads included (4096^2 in blocks of 38 x 32, one
+// step: 1.28 GB in 272 us; FP64 24 x 20, one step 2.65 GB in 497; 3000^2 at two
+// steps 766 MB in 174, where the fitted model says 149).
+inline double hbm_time(int es, double all_cells, double cells_moved) {
+  return all_cells * 18 * es > 256e6 ? cells_moved * 9 * es / (es == 4 ? 4.5e6 : 5.0e6) : 0.0;
+}
+
 // The plan of least modelled time per step for `rows` rows of a lattice; max_k
 // bounds the steps of a launch (min_k of a launch that must take that many).
 inline BlockPlan plan_lattice(int nx, int rows, int es, int cus, int min_k, int max_k, double* us_per_step) {
@@ -176,8 +185,9 @@ inline BlockPlan plan_lattice(int nx, int rows, int es, int cus, int min_k, int 
           if (nty < fewest || (round > 0 && nty == fewest)) continue;
           const int halo = 2 * (2 * k - 1), w = (nx + ntx - 1) / ntx, h = (rows + nty - 1) / nty;
           const double q = (double)(((long long)ntx * nty + cus - 1) / cus);
-          const double t = block_launch_time(c, k, q, block_work(c, w + halo, h + halo, k),
-                                             (double)(w + halo) * (h + halo) + (double)w * h, r) / k;
+          const double moved = (double)(w + halo) * (h + halo) + (double)w * h;
+          const double t = std::max(block_launch_time(c, k, q, block_work(c, w + halo, h + halo, k), moved, r),
+                                    hbm_time(es, (double)nx * rows, ntx * nty * moved)) / k;
           if (t < least) {
             least = t;
             best = block_plan(nx, rows, k, ntx, nty, s);
@@ -280,13 +290,8 @@ inline BlockCut cut_domain(const BlockCost& c, const DomainSize& d, BlockShape s
 // Blocks of domains far smaller than a workgroup wait twice for their start and chain,
 // shared by the r workgroups of a CU (2,000 domains of 3^2 beside a 1500^2).
 //
-// A batch whose two buffers pass the 256 MB last-level cache moves its cells at the
-// rate of HBM: a launch takes at least its loads and stores at 4.5 TB/s (FP32) or
-// 5.0 (FP64), the halos' second reads included (4096^2 in blocks of 38 x 32, one
-// step: 1.28 GB in 272 us; FP64 24 x 20, one step 2.65 GB in 497; 3000^2 at two
-// steps 766 MB in 174, where the fitted model says 149).  And beyond
-// block_beyond_cache the FP64 model is 1.16 times what is measured (1448^2 to 4096^2,
-// 60 to 240 domains of 200^2, uneven ones: 1.13 to 1.19).
+// Beyond block_beyond_cache the FP64 model is 1.16 times what is measured (1448^2 to
+// 4096^2, 60 to 240 domains of 200^2, uneven ones: 1.13 to 1.19).
 struct BatchLaunchCost {
   int es, k, resident;
   double blocks = 0.0, work = 0.0, cells = 0.0, busy = 0.0;
@@ -305,8 +310,7 @@ struct BatchLaunchCost {
     double t = q <= resident ? block_launch_time(c, k, q, work / blocks, cells / blocks, resident)
                              : c.start + q * busy / blocks;
     if (block_beyond_cache(es, (long long)all_cells) && es == 8) t *= 0.86;
-    if (all_cells * 18 * es > 256e6) t = std::max(t, cells * 9 * es / (es == 4 ? 4.5e6 : 5.0e6));
-    return t;
+    return std::max(t, hbm_time(es, all_cells, cells));
   }
 };
 

@@ -1,5 +1,6 @@
-"""Block plans of batches of mixed sizes (lbm_plan.h): the choice of steps and shape, which the
-cover and capacity checks of test_block_launch.py leave open."""
+"""Block plans of batches of mixed sizes and of lattices beyond the last-level cache (lbm_plan.h):
+the choice of steps and shape, which the cover and capacity checks of test_block_launch.py
+leave open."""
 import os
 import shutil
 import subprocess
@@ -9,11 +10,12 @@ import pytest
 from test_persistent_protocol import CSRC, PROTO, ROOT
 
 
-def test_plans_of_mixed_batches_see_every_domain(tmp_path):
+@pytest.mark.parametrize("harness", ["batch_plan", "lattice_far"])
+def test_plans_of_mixed_batches_and_large_lattices(tmp_path, harness):
     exe, rocm = str(tmp_path / "plans"), "/opt/rocm/include"
     if not os.path.isdir(rocm) or shutil.which("g++") is None:
         pytest.skip("no HIP headers or g++")
     subprocess.check_call(["g++", "-O2", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", rocm, "-I",
-                           os.path.join(ROOT, "include"), "-I", CSRC, "-o", exe, os.path.join(PROTO, "batch_plan.cpp")])
+                           os.path.join(ROOT, "include"), "-I", CSRC, "-o", exe, os.path.join(PROTO, f"{harness}.cpp")])
     res = subprocess.run([exe], capture_output=True, text=True, timeout=300)
     assert res.returncode == 0 and "0 failures" in res.stdout, res.stdout + res.stderr
