@@ -1249,15 +1249,27 @@ BatchRun batch_run(const lbm_batch* b, int nsteps, int parity) {
   return r;
 }
 
-// Steps of one block launch: a whole-domain launch takes any number, bounded
-// so that one kernel stays short.
-int block_steps_max(const lbm_batch* b) { return b->blocks.whole ? 4096 : b->blocks.k; }
+// Steps of one whole-domain launch: it takes any number, bounded so that one kernel
+// stays short.
+constexpr int kWholeSteps = 4096;
 
 // Buffer swaps that n steps take: one per block launch, or one per step, or one
 // per pair of steps and one for an odd last step.
 int batch_launches(const lbm_batch* b, int n) {
-  if (b->blocks.k > 0) return (n + block_steps_max(b) - 1) / block_steps_max(b);
+  if (b->blocks.k > 0) return b->blocks.whole ? (n + kWholeSteps - 1) / kWholeSteps : b->blocks.launches(n);
   return b->fuse == 2 ? n / 2 + n % 2 : n;
+}
+
+// One launch of one or two steps over the tiles.
+hipError_t batch_tiles(lbm_batch* b, int steps, int parity) {
+  BatchRun r = batch_run(b, steps, parity);
+  if (steps == 1) {
+    r.grid = b->ntile_total;
+    return launch_batch(b->prec, b->eos, b->tile_x, r, b->stream);
+  }
+  r.tiles = b->d_tiles2;
+  r.grid = b->ntile2_total;
+  return launch_batch_step2(b->prec, b->eos, b->tile_x, r, b->stream);
 }
 
 // Enqueues n steps: persistent = queue/counter reset, one launch of n / 2
@@ -1279,26 +1291,21 @@ hipError_t batch_enqueue(lbm_batch* b, int n) {
     launch = pairs;
     left = n - 2 * pairs;
   } else if (b->blocks.k > 0) {
-    for (const int most = block_steps_max(b); left > 0 && e == hipSuccess; ++launch) {
-      const int k = std::min(left, most);
-      e = launch_batch_block(b->prec, b->eos,
-                             {b->d_dom, b->d_blocks, b->nblocks, b->blocks.shape.threads, b->blocks.shape.cells,
-                              (b->parity + launch) & 1, k, b->blocks.whole}, b->stream);
-      left -= k;
+    for (; left > 0 && e == hipSuccess; ++launch) {
+      const int parity = (b->parity + launch) & 1;
+      const BatchLaunch q = b->blocks.whole ? BatchLaunch{std::min(left, kWholeSteps), false} : b->blocks.next(left);
+      if (q.tiles)
+        e = batch_tiles(b, q.steps, parity);
+      else
+        e = launch_batch_block(b->prec, b->eos,
+                               {b->d_dom, b->d_blocks, b->nblocks, b->blocks.shape.threads, b->blocks.shape.cells,
+                                parity, q.steps, b->blocks.whole}, b->stream);
+      left -= q.steps;
     }
   } else if (b->fuse == 2) {
-    for (; left >= 2 && e == hipSuccess; left -= 2, ++launch) {
-      BatchRun r = batch_run(b, 2, (b->parity + launch) & 1);
-      r.tiles = b->d_tiles2;
-      r.grid = b->ntile2_total;
-      e = launch_batch_step2(b->prec, b->eos, b->tile_x, r, b->stream);
-    }
+    for (; left >= 2 && e == hipSuccess; left -= 2, ++launch) e = batch_tiles(b, 2, (b->parity + launch) & 1);
   }
-  for (; left > 0 && e == hipSuccess; --left, ++launch) {
-    BatchRun r = batch_run(b, 1, (b->parity + launch) & 1);
-    r.grid = b->ntile_total;
-    e = launch_batch(b->prec, b->eos, b->tile_x, r, b->stream);
-  }
+  for (; left > 0 && e == hipSuccess; --left, ++launch) e = batch_tiles(b, 1, (b->parity + launch) & 1);
   return e;
 }
 

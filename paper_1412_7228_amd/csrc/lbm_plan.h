@@ -203,6 +203,19 @@ inline BlockPlan plan_lattice(int nx, int rows, int es, int cus, int min_k, int 
 // ---------------------------------------------------------------------------
 // Batches
 // ---------------------------------------------------------------------------
+// One launch of a batch: its steps, by blocks or by the marching tiles.
+struct BatchLaunch {
+  int steps;
+  bool tiles;
+};
+
+// What a call does with its last steps, at most 2 k of them: the next launch for
+// each number of steps left, and the launches that number takes in all.
+struct BatchTail {
+  BatchLaunch next[2 * kBlockMaxSteps + 1];
+  int launches[2 * kBlockMaxSteps + 1];
+};
+
 // Block launches of a batch: every domain's blocks in one launch of k steps
 // (domain d in ntx[d] x nty[d] of them), or, with `whole`, every domain whole
 // in one workgroup, any number of steps a launch.  k = 0: marching tiles.
@@ -212,6 +225,15 @@ struct BatchBlocks {
   BlockShape shape{};
   std::vector<int> ntx, nty;
   double us_per_step = 1e300, tiles_us_per_step = 1e300;  // modelled; the tiles' of the default shape
+  BatchTail tail{};
+
+  // The next launch of a call with `left` steps to go, and a call's launches
+  // (not of whole domains).
+  BatchLaunch next(int left) const { return left > 2 * k ? BatchLaunch{k, false} : tail.next[left]; }
+  int launches(int n) const {
+    const int full = n > 2 * k ? (n - k - 1) / k : 0;
+    return full + tail.launches[n - full * k];
+  }
 };
 
 struct DomainSize {
@@ -314,19 +336,50 @@ struct BatchLaunchCost {
   }
 };
 
-// A two-step launch of the marching tiles of the default shape (256 lanes by 16
-// rows, 250 columns stored): so much a tile and so much a cell, and at least a
-// tile's chain of rows.  Fitted to 34 batches (one domain of 1024^2 to 4,000 of
-// 50^2) within 5% rms.
-inline double batch_tiles_time(const std::vector<DomainClass>& classes, int es) {
-  const int w = 256 - kStep2Halo;
+// A launch of the marching tiles of the default shape (256 lanes by 16 rows, of which
+// a two-step launch stores 250 columns): so much a tile and so much a cell, and at
+// least a tile's chain of rows.  Fitted to 34 batches (one domain of 1024^2 to
+// 4,000 of 50^2) within 5% rms (two steps) and 6 to 9% (one).
+inline double batch_tiles_time(const std::vector<DomainClass>& classes, int es, int steps) {
+  const int w = steps == 2 ? 256 - kStep2Halo : 256;
   double tiles = 0.0, cells = 0.0;
   for (const auto& q : classes) {
     tiles += q.count * ((q.size.nx + w - 1) / w) * ((q.size.ny + 15) / 16);
     cells += q.count * q.cells();
   }
-  return es == 4 ? std::max(35.0, 10.4 + 31.5e-3 * tiles + 8.1e-6 * cells)
-                 : std::max(41.0, 21.3 + 79.5e-3 * tiles + 11.9e-6 * cells);
+  if (steps == 2)
+    return es == 4 ? std::max(35.0, 10.4 + 31.5e-3 * tiles + 8.1e-6 * cells)
+                   : std::max(41.0, 21.3 + 79.5e-3 * tiles + 11.9e-6 * cells);
+  return es == 4 ? std::max(22.0, 16.6e-3 * tiles + 11.2e-6 * cells)
+                 : std::max(26.0, 9.7 + 38.0e-3 * tiles + 18.3e-6 * cells);
+}
+
+// The launches of the last steps of a call: a block launch of as many as there are, or
+// the tiles where they take less: a launch of fewer steps than k loads and stores as
+// much for less work, and large batches of wide domains are faster on the tiles then
+// (4096^2 FP32, us a step: one step by blocks 278, by tiles 239; two 163 / 141; four as
+// three and one 168, as two and two by tiles 139; 1,000 domains of 64^2, whose tiles are
+// three quarters idle, one step 78 / 118).  The models' ratio misses what 31 batches of
+// 50 us a step and more measured by up to a sixth; one step goes to the tiles where
+// theirs is below 0.925 (below that 0.84 to 1.01 measured and once 1.07, above it up to
+// 1.09), two below 1.02 (0.84 to 1.01).
+inline BatchTail plan_tail(int k, const double (&block_us)[kBlockMaxSteps + 1], double tile1_us, double tile2_us) {
+  BatchTail tail{};
+  double cost[2 * kBlockMaxSteps + 1] = {};
+  for (int m = 1; m <= 2 * k; ++m) {
+    cost[m] = 1e300;
+    auto take = [&](int steps, bool tiles, double us) {
+      if (us + cost[m - steps] >= cost[m]) return;
+      cost[m] = us + cost[m - steps];
+      tail.next[m] = {steps, tiles};
+      tail.launches[m] = 1 + tail.launches[m - steps];
+    };
+    const double margin = m > k ? 1.04 : 1.0;
+    take(std::min(m, k), false, block_us[std::min(m, k)]);
+    if (m >= 2) take(2, true, tile2_us * 0.98 * margin);
+    take(1, true, tile1_us * 1.08 * margin);
+  }
+  return tail;
 }
 
 // Steps and shape from at most 16 classes that stand for the batch, then every
@@ -386,10 +439,23 @@ inline BatchBlocks plan_batch(const std::vector<DomainSize>& dom, int es, int cu
     cuts.push_back(cut_domain(c, d.size, best.shape, best.k, finer));
     if (cuts.back().ntx == 0) return BatchBlocks{};  // a domain that the chosen blocks do not fit: marching tiles
   }
-  BatchLaunchCost sums{es, best.k, block_resident(es, best.shape)};
-  for (size_t q = 0; q < classes.size(); ++q) sums.add(cuts[q], classes[q].count);
-  best.us_per_step = sums.us(all_cells, cus) / best.k;
-  best.tiles_us_per_step = batch_tiles_time(classes, es) / 2;
+  // the time of a launch of each number of steps by these blocks
+  double block_us[kBlockMaxSteps + 1] = {};
+  for (int k = 1; k <= best.k; ++k) {
+    BatchLaunchCost sums{es, k, block_resident(es, best.shape)};
+    for (size_t q = 0; q < classes.size(); ++q) {
+      const DomainSize& d = classes[q].size;
+      const int halo = 2 * (2 * k - 1), ntx = cuts[q].ntx, nty = cuts[q].nty;
+      const int w = (d.nx + ntx - 1) / ntx, h = (d.ny + nty - 1) / nty;
+      sums.add({ntx, nty, ntx * nty * block_work(c, w + halo, h + halo, k),
+                (double)ntx * nty * ((double)(w + halo) * (h + halo) + (double)w * h)}, classes[q].count);
+    }
+    block_us[k] = sums.us(all_cells, cus);
+  }
+  const double tile2_us = batch_tiles_time(classes, es, 2);
+  best.us_per_step = block_us[best.k] / best.k;
+  best.tiles_us_per_step = tile2_us / 2;
+  best.tail = plan_tail(best.k, block_us, batch_tiles_time(classes, es, 1), tile2_us);
   for (int q : of) {
     best.ntx.push_back(cuts[q].ntx);
     best.nty.push_back(cuts[q].nty);

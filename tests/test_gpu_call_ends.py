@@ -29,6 +29,10 @@ def test_lattice_rule_takes_the_faster_launch(tmp_path):
     _harness(tmp_path, "lattice_rest.cpp")
 
 
+def test_batch_rule_takes_the_faster_launches(tmp_path):
+    _harness(tmp_path, "batch_tail.cpp")
+
+
 # blocks for every rest; one step by tiles (FP32); one (FP32) or both (FP64); both; idle lanes keep the blocks
 @pytest.mark.gpu
 @pytest.mark.parametrize("precision", ["fp32", "fp64"])
@@ -47,3 +51,29 @@ def test_lattice_calls_of_few_steps_equal_single_steps(lbm, precision, nx, ny): 
         a.step(n)
         b.step(n)
         assert _same(a, b), n
+
+
+# wide domains, whose calls of few steps go to the tiles; uneven ones; narrow ones, which keep the blocks
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("sizes", [[(1024, 1000)] * 8, [(2000, 1500), (300, 200), (64, 64)], [(70, 60)] * 900])
+def test_batch_calls_of_few_steps_equal_single_steps(lbm, precision, sizes):  # noqa: F811
+    from paper_1412_7228_amd import inputs
+
+    print(f"[gpu-case] batch calls of few steps {sizes[0]} x {len(sizes)} {precision}", flush=True)
+    cfgs = [dict(MODELS["cs"], nx=x, ny=y, kappa=0.1 * (i % 8), precision=precision) for i, (x, y) in enumerate(sizes)]
+    b = lbm.Batch(cfgs)
+    rhos = {}
+    for i, s in enumerate(sizes):
+        rhos.setdefault(s, inputs.spinodal(*s, MEAN["cs"], noise=1e-2, seed=3))
+        b.init_field(i, rhos[s])
+    calls = (1, 1, 2, 3, 4, 5, 7, 8, 10, 1)
+    for n in calls:
+        b.step(n)
+    b.sync()
+    for i in sorted({0, len(sizes) // 2, len(sizes) - 1}):
+        lat = lbm.Lattice(cfgs[i])
+        lat.set_launch(0, 0, 1)
+        lat.init_field(rhos[sizes[i]])
+        lat.step(sum(calls))
+        assert np.array_equal(b.f_soa(i), lat.f_soa(), equal_nan=True), i
