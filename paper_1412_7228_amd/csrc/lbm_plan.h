@@ -56,11 +56,16 @@ inline int block_resident(int es, BlockShape s) {
 }
 
 // CU time of the phases of a block of W x H cells, halo included.
-inline double block_work(const BlockCost& c, int W, int H, int k) {
-  auto waves = [&](int rim) { return ((H - rim) * W + 63) / 64 - rim * W / 64; };
+inline double block_work(const BlockCost& c, unsigned W, unsigned H, int k) {
+  auto waves = [&](unsigned rim) { return (int)(((H - rim) * W + 63) / 64 - rim * W / 64); };
   double t = 0.0;
   for (int s = 0; s < k; ++s) t += c.density * waves(2 * s) + c.collide * waves(2 * s + 1);
   return t;
+}
+
+// At most that: every phase takes the stored cells.
+inline double block_work_least(const BlockCost& c, double stored, int k) {
+  return k * (c.density + c.collide) * stored * (1.0 / 64.0);
 }
 
 inline double block_launch_time(const BlockCost& c, int k, double q, double work, double cells_moved, int r) {
@@ -168,36 +173,67 @@ inline BlockPlan plan_lattice(int nx, int rows, int es, int cus, int min_k, int 
   const BlockCost c = block_cost(es);
   const bool far = block_beyond_cache(es, (long long)nx * rows);
   if (far) min_k = std::max(min_k, 3);
-  BlockPlan best{};
-  double least = 1e300;
-  for (BlockShape s : kBlockShapes) {
-    if (!block_shape_built(es, s)) continue;
-    const int r = block_resident(es, s);
-    if (far && r < 2) continue;
-    for (int k = max_k; k >= min_k; --k) {
-      if (c.start + k * c.step / r > least * k) continue;  // not even the latency fits
-      for_block_widths(nx, [&](int ntx) {
+  constexpr int kShapes = sizeof kBlockShapes / sizeof *kBlockShapes;
+  BlockPlan best[kShapes] = {};
+  double least[kShapes], any = 1e300;  // of each shape, and of all
+  for (double& t : least) t = 1e300;
+  // one division of the lattice, its time by any shape
+  struct Division {
+    int nty;
+    double q, moved, work;  // work < 0: not yet formed
+  };
+  // A context is made for every lattice of a sweep, so the search itself counts (200^2
+  // FP32 25 us of host time, 35 when every division's time is formed): what shapes
+  // share is formed once, and a division's work only where its least possible time
+  // is not above the best yet.
+  for (int k = max_k; k >= min_k; --k) {
+    const int halo = 2 * (2 * k - 1);
+    for_block_widths(nx, [&](int ntx) {
+      const int w = (nx + ntx - 1) / ntx;
+      auto division = [&](int nty) {
+        const int h = (rows + nty - 1) / nty;
+        return Division{nty, (double)(((long long)ntx * nty + cus - 1) / cus),
+                        (double)(w + halo) * (h + halo) + (double)w * h, -1.0};
+      };
+      // as many blocks as the CUs take in one to four rounds
+      Division rounds[4];
+      int formed = 0, round_nty[4];
+      for (int round = 1; round <= 4; ++round) round_nty[round - 1] = std::min(rows, round * cus / ntx);
+      for (int i = 0; i < kShapes; ++i) {
+        const BlockShape s = kBlockShapes[i];
+        if (!block_shape_built(es, s)) continue;
+        const int r = block_resident(es, s);
+        if (far && r < 2) continue;
+        if (c.start + k * c.step / r > any * k) continue;  // not even the latency fits
         const int fewest = block_rows(nx, rows, ntx, k, s.threads * s.cells);
-        if (fewest == 0) return;
-        // the fewest blocks, or as many as the CUs take in one to four rounds
-        for (int round = 0; round <= 4; ++round) {
-          const int nty = round == 0 ? fewest : std::min(rows, round * cus / ntx);
-          if (nty < fewest || (round > 0 && nty == fewest)) continue;
-          const int halo = 2 * (2 * k - 1), w = (nx + ntx - 1) / ntx, h = (rows + nty - 1) / nty;
-          const double q = (double)(((long long)ntx * nty + cus - 1) / cus);
-          const double moved = (double)(w + halo) * (h + halo) + (double)w * h;
-          const double t = std::max(block_launch_time(c, k, q, block_work(c, w + halo, h + halo, k), moved, r),
-                                    hbm_time(es, (double)nx * rows, ntx * nty * moved)) / k;
-          if (t < least) {
-            least = t;
-            best = block_plan(nx, rows, k, ntx, nty, s);
-          }
+        if (fewest == 0) continue;
+        auto take = [&](Division& d) {
+          const int h = (rows + d.nty - 1) / d.nty;
+          const double stored = (double)w * h, hbm = hbm_time(es, (double)nx * rows, ntx * d.nty * d.moved);
+          if (std::max(block_launch_time(c, k, d.q, block_work_least(c, stored, k), d.moved, r), hbm) > any * k) return;
+          if (d.work < 0.0) d.work = block_work(c, w + halo, h + halo, k);
+          const double t = std::max(block_launch_time(c, k, d.q, d.work, d.moved, r), hbm) / k;
+          if (t >= least[i]) return;
+          least[i] = t;
+          any = std::min(any, t);
+          best[i] = block_plan(nx, rows, k, ntx, d.nty, s);
+        };
+        Division fewest_blocks = division(fewest);
+        take(fewest_blocks);
+        for (int q = 0; q < 4; ++q) {
+          if (round_nty[q] <= fewest) continue;
+          if (!(formed & 1 << q)) rounds[q] = division(round_nty[q]);
+          formed |= 1 << q;
+          take(rounds[q]);
         }
-      });
-    }
+      }
+    });
   }
-  if (us_per_step) *us_per_step = least;
-  return best;
+  int shape = 0;
+  for (int i = 1; i < kShapes; ++i)
+    if (least[i] < least[shape]) shape = i;
+  if (us_per_step) *us_per_step = least[shape];
+  return best[shape];
 }
 
 // ---------------------------------------------------------------------------
@@ -301,9 +337,12 @@ inline BlockCut cut_domain(const BlockCost& c, const DomainSize& d, BlockShape s
     if (fewest == 0) return;
     const int nty = std::min(d.ny, fewest * finer);
     const int w = (d.nx + ntx - 1) / ntx, h = (d.ny + nty - 1) / nty;
-    const BlockCut q{ntx, nty, ntx * nty * block_work(c, w + halo, h + halo, k),
-                     (double)ntx * nty * ((double)(w + halo) * (h + halo) + (double)w * h)};
-    if (q.work + c.hide * c.moved * q.cells < best.work + c.hide * c.moved * best.cells) best = q;
+    const double n = (double)ntx * nty, stored = (double)w * h;
+    BlockCut q{ntx, nty, n * block_work_least(c, stored, k), n * ((double)(w + halo) * (h + halo) + stored)};
+    auto better = [&] { return q.work + c.hide * c.moved * q.cells < best.work + c.hide * c.moved * best.cells; };
+    if (!better()) return;
+    q.work = ntx * nty * block_work(c, w + halo, h + halo, k);
+    if (better()) best = q;
   });
   return best;
 }

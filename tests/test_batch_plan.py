@@ -1,5 +1,5 @@
 """Block plans of batches of mixed sizes and of lattices beyond the last-level cache (lbm_plan.h):
-the choice of steps and shape, which the cover and capacity checks of test_block_launch.py
+the choice of steps and shape and its search, which the cover and capacity checks of test_block_launch.py
 leave open."""
 import os
 import shutil
@@ -10,8 +10,8 @@ import pytest
 from test_persistent_protocol import CSRC, PROTO, ROOT
 
 
-@pytest.mark.parametrize("harness", ["batch_plan", "lattice_far"])
-def test_plans_of_mixed_batches_and_large_lattices(tmp_path, harness):
+@pytest.mark.parametrize("harness", ["batch_plan", "lattice_far", "plan_search"])
+def test_plans(tmp_path, harness):
     exe, rocm = str(tmp_path / "plans"), "/opt/rocm/include"
     if not os.path.isdir(rocm) or shutil.which("g++") is None:
         pytest.skip("no HIP headers or g++")
