@@ -48,16 +48,24 @@ def initial_density(case: dict, cfg: dict) -> np.ndarray:
                           noise=float(case.get("noise", 1e-3)), seed=int(case.get("seed", 0)))
 
 
+def default_tile(steps_per_pass: int) -> tuple:
+    """The batch tile of the studies: the library's own launch with two steps per pass; single-step
+    passes have one kernel, for which 128 x 16 is faster than the library's default shape (60
+    droplets of 200^2 FP32 35 us a step against 45)."""
+    return (128, 16) if steps_per_pass == 1 else (0, 0)
+
+
 def run_cases(cases: list, steps: int, precision: str = "fp32", mode: str = "per_step",
-              tile: tuple = (0, 0), chunk: int = 5000, steps_per_pass: int = 2,
+              tile: tuple | None = None, chunk: int = 5000, steps_per_pass: int = 2,
               rhos: list | None = None) -> list:
     """Runs every case for `steps` steps in one batch; returns one result dict per case
     (the observables plus ``ok``: finite, positive densities, no U > 0 cell, a drop
-    denser than its surroundings).  ``tile`` (0, 0) is the library's default launch.  ``rhos``: initial densities, one per case (default:
+    denser than its surroundings).  ``tile``: default :func:`default_tile`; (0, 0) is the
+    library's default shape.  ``rhos``: initial densities, one per case (default:
     :func:`initial_density`)."""
     cfgs = [case_config(c, precision) for c in cases]
     b = lbm.Batch(cfgs)
-    b.set_launch(mode, *tile, steps_per_pass=steps_per_pass)
+    b.set_launch(mode, *(tile or default_tile(steps_per_pass)), steps_per_pass=steps_per_pass)
     for i, (c, cfg) in enumerate(zip(cases, cfgs)):
         b.init_field(i, initial_density(c, cfg) if rhos is None else rhos[i])
     left = steps

@@ -45,9 +45,9 @@ def _finite(x):
     return float(x) if np.isfinite(x) else None
 
 
-def _run_batch(cfgs, rhos, steps, tile=(0, 0), chunk=5000, steps_per_pass=2):
+def _run_batch(cfgs, rhos, steps, tile=None, chunk=5000, steps_per_pass=2):
     b = lbm.Batch(cfgs)
-    b.set_launch("per_step", *tile, steps_per_pass=steps_per_pass)
+    b.set_launch("per_step", *(tile or laplace.default_tile(steps_per_pass)), steps_per_pass=steps_per_pass)
     for i, r in enumerate(rhos):
         b.init_field(i, r)
     left = steps
