@@ -1080,9 +1080,10 @@ struct lbm_batch {
   int parity = 0;
   int64_t step = 0;
   bool layout_ok = false;  // the device tile lists match mode / tile / fuse
-  // graph cache
-  hipGraphExec_t exec = nullptr;
-  int exec_mode = -1, exec_steps = 0, exec_parity = -1, exec_fuse = 0;
+  // the graph of a call's launches from either buffer (a call of an odd number of
+  // launches ends on the other one), for exec_steps[parity] steps
+  hipGraphExec_t exec[2] = {};
+  int exec_steps[2] = {};
   // FP64 scratch of the fields and the observables, allocated with the first state
   double* work = nullptr;    // device: 4 fields of the largest domain, then the arrays of `obs`
   ObsBatch obs{};
@@ -1098,9 +1099,10 @@ namespace {
 constexpr bool kPersistentEnabled = true;
 
 void batch_free_layout(lbm_batch* b) {
-  if (b->exec) (void)hipGraphExecDestroy(b->exec);
-  b->exec = nullptr;
-  b->exec_mode = -1;
+  for (hipGraphExec_t& exec : b->exec) {
+    if (exec) (void)hipGraphExecDestroy(exec);
+    exec = nullptr;
+  }
   for (void* q : {b->d_dom, b->d_tiles, b->d_tiles2, b->d_blocks, (void*)b->d_group_begin})
     if (q) (void)hipFree(q);
   b->d_dom = b->d_tiles = b->d_tiles2 = b->d_blocks = nullptr;
@@ -1309,14 +1311,13 @@ hipError_t batch_enqueue(lbm_batch* b, int n) {
   return e;
 }
 
-// The same n steps captured once as a graph (re-captured when the mode, the
-// step count or the buffer parity changes).
+// The same n steps captured once as a graph for the current buffer (captured again
+// when the step count changes; a new layout drops both graphs).
 lbm_status batch_graph(lbm_batch* b, int n) {
-  if (b->exec && b->exec_mode == b->mode && b->exec_steps == n && b->exec_parity == b->parity &&
-      b->exec_fuse == b->fuse)
-    return LBM_OK;
-  if (b->exec) (void)hipGraphExecDestroy(b->exec);
-  b->exec = nullptr;
+  hipGraphExec_t& exec = b->exec[b->parity];
+  if (exec && b->exec_steps[b->parity] == n) return LBM_OK;
+  if (exec) (void)hipGraphExecDestroy(exec);
+  exec = nullptr;
   hipGraph_t graph = nullptr;
   HIP_TRY(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
   hipError_t e = batch_enqueue(b, n);
@@ -1325,13 +1326,13 @@ lbm_status batch_graph(lbm_batch* b, int n) {
     if (graph) (void)hipGraphDestroy(graph);
     return fail(LBM_EDEVICE, "batch graph capture: %s", hipGetErrorString(e != hipSuccess ? e : e2));
   }
-  e = hipGraphInstantiate(&b->exec, graph, nullptr, nullptr, 0);
+  e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
   (void)hipGraphDestroy(graph);
-  if (e != hipSuccess) return fail(LBM_EDEVICE, "hipGraphInstantiate: %s", hipGetErrorString(e));
-  b->exec_mode = b->mode;
-  b->exec_steps = n;
-  b->exec_parity = b->parity;
-  b->exec_fuse = b->fuse;
+  if (e != hipSuccess) {
+    exec = nullptr;
+    return fail(LBM_EDEVICE, "hipGraphInstantiate: %s", hipGetErrorString(e));
+  }
+  b->exec_steps[b->parity] = n;
   return LBM_OK;
 }
 
@@ -1563,7 +1564,7 @@ lbm_status lbm_batch_step(lbm_batch* b, int64_t n) {
       // graphs cannot be captured on the legacy null stream: only on a real stream
       lbm_status st = batch_graph(b, k);
       if (st != LBM_OK) return st;
-      HIP_TRY(hipGraphLaunch(b->exec, b->stream));
+      HIP_TRY(hipGraphLaunch(b->exec[b->parity], b->stream));
     } else {
       HIP_TRY(batch_enqueue(b, k));
     }

@@ -1,6 +1,6 @@
-// Loaded into the global scope before the HIP runtime: hipMalloc and hipHostMalloc
-// are counted and passed on, or (shim_refuse_pinned) pinned memory is refused as a
-// system without any left would.
+// Loaded into the global scope before the HIP runtime: hipMalloc, hipHostMalloc and
+// hipGraphInstantiate are counted and passed on, or (shim_refuse_pinned) pinned memory
+// is refused as a system without any left would.
 #include <dlfcn.h>
 #include <link.h>
 
@@ -8,7 +8,7 @@
 #include <cstring>
 #include <string>
 
-static int mallocs, pinned, refuse;
+static int mallocs, pinned, graphs, refuse;
 
 static void* real(const char* name) {
   static std::string path;
@@ -37,6 +37,13 @@ int hipHostMalloc(void** p, size_t n, unsigned flags) {
   return refuse ? 2 : f(p, n, flags);  // 2: hipErrorOutOfMemory
 }
 
+int hipGraphInstantiate(void** exec, void* graph, void* node, char* log, size_t n) {
+  static auto f = reinterpret_cast<int (*)(void**, void*, void*, char*, size_t)>(real("hipGraphInstantiate"));
+  ++graphs;
+  return f(exec, graph, node, log, n);
+}
+
+int shim_graphs() { return graphs; }
 int shim_mallocs() { return mallocs; }
 int shim_pinned() { return pinned; }
 void shim_refuse_pinned(int on) { refuse = on; }

@@ -1,5 +1,5 @@
-"""When the library allocates: its calls of hipMalloc and hipHostMalloc counted (in a process of
-their own, through a shim in the global scope)."""
+"""When the library allocates and makes graphs: its calls of hipMalloc, hipHostMalloc and
+hipGraphInstantiate counted (in a process of their own, through a shim in the global scope)."""
 import json
 import os
 import subprocess
@@ -92,3 +92,30 @@ out["asked"] = shim.shim_pinned() - before
 out["same"] = [bool(np.array_equal(x, y, equal_nan=True)) for x, y in zip(a, b)]
 """)
     assert r["asked"] >= 3 and all(r["same"]) and len(r["same"]) == 14, r
+
+
+def test_repeated_batch_calls_replay_their_graphs(tmp_path):
+    """Equal calls make at most one graph for each buffer they start from, also where a call is an odd
+    number of launches and so ends on the other buffer: blocks (several steps a launch), whole
+    domains (one launch), tiles of one and two steps; and the states are those of one call."""
+    print("[gpu-case] graphs of repeated batch calls", flush=True)
+    r = _run(tmp_path, """
+for name, sizes, launch in (("blocks", [200] * 4, None), ("whole", [20, 40], None), ("tiles", [200] * 4, (128, 16, 2)),
+                            ("single", [200] * 4, (64, 16, 1))):
+    for n in (1, 3, 5, 8):
+        b, once = (lbm.Batch([dict(cfg, nx=s, ny=s) for s in sizes]) for _ in range(2))
+        for q in (b, once):
+            if launch:
+                q.set_launch("per_step", launch[0], launch[1], steps_per_pass=launch[2])
+            for i, s in enumerate(sizes):
+                q.init_field(i, inputs.spinodal(s, s, 0.16, seed=1))
+        before = shim.shim_graphs()
+        for _ in range(6):
+            b.step(n)
+        b.sync()
+        out[f"{name} {n}"] = shim.shim_graphs() - before
+        once.step(6 * n)
+        out[f"{name} {n} same"] = int(np.array_equal(b.f_soa(0), once.f_soa(0)))
+""")
+    assert all(v == 1 for k, v in r.items() if k.endswith("same")), r
+    assert all(v <= 2 for k, v in r.items() if not k.endswith("same")), r
