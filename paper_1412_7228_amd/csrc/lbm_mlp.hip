@@ -35,6 +35,7 @@ constexpr int kNP = oB4 + kOut;  // 33,923
 static_assert(kNP == 33923, "parameter count");
 
 constexpr int kPad = kH + 4;  // row stride of the LDS activations: lanes (row i, term kk) on bank 4 i + kk
+static_assert(kPad * sizeof(float) % 16 == 0, "rows are read four values at a time");
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -234,8 +235,8 @@ __global__ void __launch_bounds__(kThreads)
                  const float* __restrict__ master, const unsigned short* __restrict__ wb,
                  const unsigned short* __restrict__ wp, const Acts acts, float* __restrict__ dx,
                  float* __restrict__ y_out) {
-  __shared__ float h[3][kBlockRows][kPad];    // h1, h2, h3
-  __shared__ float dzs[2][kBlockRows][kPad];  // gradients at two layers' pre-activations
+  __shared__ alignas(16) float h[3][kBlockRows][kPad];    // h1, h2, h3
+  __shared__ alignas(16) float dzs[2][kBlockRows][kPad];  // gradients at two layers' pre-activations
   __shared__ float w4[kOut][kH];
   __shared__ float xs[kBlockRows][kIn], ys[kBlockRows][kOut], dys[kBlockRows][kOut];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i = lane & 15, kk = lane >> 4;
