@@ -136,11 +136,12 @@ typedef struct {
  * number of waves of the device (two such workgroups per CU).
  * With the default shape (a new context, or both tile fields 0 and two steps
  * per pass) lbm_step is free to fuse more steps: lattices up to 12 * 2^20
- * cells (FP32) or 2^20 cells (FP64) run block launches of 2 to 6 steps, each
- * block of the lattice held in one workgroup's registers and LDS; the states
- * are bitwise those of the tiles.  So do the two-step launches of lbm_step_rows
- * over up to 1.5 * 2^20 (FP32) or 2^20 cells.  A shape asked for is the shape
- * that runs; lbm_get_launch reports the two-step shape throughout. */
+ * cells (FP32) or 7 * 2^20 cells (FP64) run block launches of 2 to 6 steps, each
+ * block of the lattice held in one workgroup's registers and LDS; one or two
+ * steps that end a call may go to the tiles; the states are bitwise those of the
+ * tiles.  So do the two-step launches of lbm_step_rows over up to 1.5 * 2^20
+ * (FP32) or 2^20 cells.  A shape asked for is the shape that runs;
+ * lbm_get_launch reports the two-step shape throughout. */
 typedef struct {
   int32_t tile_x, tile_y;
   int32_t steps_per_pass;
@@ -199,7 +200,10 @@ lbm_status lbm_get_launch(const lbm_ctx* ctx, lbm_launch* launch);
 
 /* Initial state f_a = W_a rho [1 + 3 e.u + 4.5 (e.u)^2 - 1.5 u^2] (moments
  * of Eq. 4), W = 4/9, 1/9, 1/36.  rho is required, ux/uy may be NULL (zero).
- * Resets the step counter.  LBM_ENONFINITE if a density is not finite or <= 0. */
+ * Resets the step counter.  The first call allocates the scratch of every
+ * read-out (32 bytes of device memory a cell and the partial sums; pinned host
+ * memory for fields of up to 2^18 cells, where the system gives it), so that no later
+ * call allocates.  LBM_ENONFINITE if a density is not finite or <= 0. */
 lbm_status lbm_init_field(lbm_ctx* ctx, const double* rho, const double* ux, const double* uy);
 
 /* Sets the distributions directly from a host array f[a][y][x] (9*nx*ny
@@ -346,10 +350,10 @@ typedef struct {
  * precisions differ. Default launch: LBM_BATCH_PER_STEP with two steps per
  * launch, 256 x 16 tiles.  With that launch (or a later one with mode
  * LBM_BATCH_PER_STEP, both tile fields 0 and two steps per launch) the steps run
- * as block launches of 2 to 6 steps (as in lbm_launch), or, where every domain
- * fits one workgroup (at most 2,048 cells), as launches that each keep a domain
- * on one CU for up to 4,096 steps; the states are bitwise the same.
- * lbm_batch_get_launch reports the tiles of the shape. */
+ * as block launches of 2 to 6 steps and tiles where those are faster (as in
+ * lbm_launch), or, where every domain fits one workgroup (at most 2,048 cells), as
+ * launches that each keep a domain on one CU for up to 4,096 steps; the states are
+ * bitwise the same.  lbm_batch_get_launch reports the tiles of the shape. */
 lbm_status lbm_batch_create(const lbm_params* params, int32_t n, void* hip_stream, lbm_batch** out);
 void lbm_batch_destroy(lbm_batch* b);
 
@@ -376,8 +380,8 @@ lbm_status lbm_batch_step(lbm_batch* b, int64_t n);
  * wait exceeded the spin limit; the state is then not a whole step). */
 lbm_status lbm_batch_sync(lbm_batch* b);
 
-/* Observables of every domain into out[0..n) (as lbm_observables); returns the
- * first fault status after filling all entries. */
+/* Observables of every domain into out[0..n), bitwise those of lbm_observables on
+ * the same state alone; returns the first fault status after filling all entries. */
 lbm_status lbm_batch_observables(lbm_batch* b, lbm_obs* out);
 
 /* One field of domain i, as lbm_get_field. */

@@ -1,5 +1,5 @@
-"""What ends a call in block launches: one or two steps that large lattices and batches leave to
-the marching tiles, where those are faster.
+"""Where block launches end: the lattice sizes above which the marching tiles run, and the one or
+two steps at the end of a call that large lattices and batches leave to them.
 
 * CPU: the rules (lbm_plan.h) against measured times.
 * GPU: bitwise the states of single steps, for every rest of a call, above and below the
@@ -51,6 +51,25 @@ def test_lattice_calls_of_few_steps_equal_single_steps(lbm, precision, nx, ny): 
         a.step(n)
         b.step(n)
         assert _same(a, b), n
+
+
+# the last and the first size on either side of block_max_cells: 12 * 2^20 cells in FP32, 7 * 2^20 in FP64
+@pytest.mark.gpu
+@pytest.mark.parametrize("precision,n", [("fp32", 3547), ("fp32", 3548), ("fp64", 2709), ("fp64", 2710)])
+def test_default_launch_at_the_limit_of_blocks(lbm, precision, n):  # noqa: F811
+    from paper_1412_7228_amd import inputs
+
+    print(f"[gpu-case] default launch {n}^2 {precision}", flush=True)
+    cfg = dict(MODELS["cs"], nx=n, ny=n, kappa=0.3, precision=precision)
+    rho = inputs.spinodal(n, n, MEAN["cs"], noise=1e-2, seed=2)
+    a, b = lbm.Lattice(cfg), lbm.Lattice(cfg)
+    b.set_launch(0, 0, 1)
+    for lat in (a, b):
+        lat.init_field(rho)
+    for steps in (3, 4, 200):  # 200: a replayed graph of three-step launches or of two-step tiles
+        a.step(steps)
+        b.step(steps)
+        assert _same(a, b), steps
 
 
 # wide domains, whose calls of few steps go to the tiles; uneven ones; narrow ones, which keep the blocks
