@@ -27,8 +27,10 @@
 // (about 0.7 us in FP32 and FP64) and a launch's 2 us, shared by its k
 // steps: 100^2 FP64 1.55 us a step against 10.2 with the tiles, 300^2 FP32 2.2
 // against 9.2.  On larger ones VALU issue, with the rim's recomputed cells as
-// the overhead (1.4 cells computed per cell stored at k = 3 in 2,048-cell FP32
-// blocks): 1000 x 700 FP32 7.5 us a step against 11.9, 2048^2 35.6 against
+// the overhead (1.3 collisions and 1.4 densities per cell stored and step at k = 3
+// in 2,048-cell FP32 blocks), and the share of a block's loads and stores that no
+// other workgroup's phases cover (a third to a half of a block's time by the model
+// of lbm_plan.h): 1000 x 700 FP32 7.5 us a step against 11.9, 2048^2 35.6 against
 // 39.9.  Register and LDS budget: FP32 blocks of 512 x 4 cells take 80 KB and 108
 // VGPRs, so two workgroups a CU cover each other's loads and stores (one of
 // 1024 x 4 in the whole LDS recomputes less and is 18% slower); 8 planes in LDS

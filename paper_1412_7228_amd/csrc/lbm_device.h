@@ -192,7 +192,7 @@ __device__ __forceinline__ typename V2<T>::t potentials(T rho, const DevC<T>& c)
 // other, with what is exact to the last bit written in the fewest operations
 // (differences shared with their negatives, factors of a power of two moved
 // into a neighbouring fused operation): 162 vector instructions of a collision
-// instead of 169, 256 domains of 64^2 to 512^2 1.9% and 4096^2 0.5% faster.
+// instead of 169, 256 domains of 64^2 to 512^2 1.9% faster (4096^2, bound by HBM too, as before).
 __device__ __forceinline__ void collide_cell(const float (&g)[9], float rho, const float (&Un)[9],
                                              const float (&Pn)[9], const DevC<float>& c, float (&out)[9]) {
   using T = float;

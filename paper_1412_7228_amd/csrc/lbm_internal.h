@@ -39,18 +39,18 @@ struct ModelConsts {
 hipError_t launch_step(lbm_precision prec, const Geometry& g, const ModelConsts& m, const void* fa,
                        void* fb, hipStream_t s);
 
-// Workgroups of the step kernel (for g.tile_x) that one CU holds at once.
 // Two fused steps per launch (lbm_step.hip): g.tile_x in {128, 256}, strips of
 // g.tile_x - 6 stored columns (g.nstrips counts them).
 hipError_t launch_step2(lbm_precision prec, const Geometry& g, const ModelConsts& m, const void* fa,
                         void* fb, hipStream_t s);
 constexpr int kStep2Halo = 6;
+// Workgroups of the step kernel (for g.tile_x) that one CU holds at once.
 hipError_t step_occupancy(lbm_precision prec, const Geometry& g, int eos, int* per_cu);
 
 // k fused steps per launch, a lattice (its rows [g.y_begin, g.y_end)) cut into
-// ntx x nty blocks each held in
-// one workgroup's registers and LDS (lbm_block.hip); k = 0: not used.  A launch
-// may take fewer steps than the plan's k (the rest of a call).
+// ntx x nty blocks each held in one workgroup's registers and LDS (lbm_block.hip);
+// k = 0: not used.  A launch may take fewer steps than the plan's k (the rest of a
+// call).
 struct BlockPlan {
   int k, ntx, nty;
   int w, h, rx, ry;    // nx = w ntx + rx, rows = h nty + ry

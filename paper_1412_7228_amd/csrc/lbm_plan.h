@@ -15,7 +15,8 @@
 // equation of state and the collision), which is what small lattices wait
 // for.  The constants are fitted to 2,150 measured launches (16^2 to 4096^2, k = 2
 // to 6, every shape) with a mean error of 4%; the plan that the model picks is
-// on average 2% slower than the best one measured, 15% at worst.
+// on average 2% slower than the best one measured, 15% at worst.  States beyond the
+// last-level cache wait for HBM besides (hbm_time, block_beyond_cache).
 #pragma once
 
 #include <algorithm>
@@ -109,8 +110,8 @@ inline long long block_max_cells(int es) { return es == 4 ? 12ll << 20 : 7ll << 
 // two steps (1700^2 55.8 us a step, at three steps 47.3) and shapes of one
 // workgroup a CU (2000 x 1500 at three steps in 512 x 4 58.9, in 512 x 2 49.2,
 // the marching tiles 51.9); 60 domains of 200^2 46.0 -> 40.7.  FP32 blocks hold twice the
-// cells and choose three steps by the model nearly everywhere (leaving two out:
-// 0.93 to 1.02 of the time at 2.2 to 3.6 million cells).
+// cells, and hbm_time alone takes two steps out where they wait (leaving them out at
+// 2.2 to 3.6 million cells too: 0.93 to 1.02 of the time).
 inline bool block_beyond_cache(int es, long long cells) { return es == 8 && cells > 1ll << 20; }
 
 // The same for a launch of two steps over some rows (lbm_step_rows), whose
