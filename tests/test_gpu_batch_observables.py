@@ -66,3 +66,31 @@ def test_workspace_of_one_large_domain_among_many_small(lbm):
     for o, rho in ((obs[0], small), (obs[2999], small), (obs[3000], large)):
         assert abs(o["mass"] - rho.sum()) <= rho.size * 2.0 ** -23 * 1.1  # nine FP32 populations a cell
         assert abs(o["rho_max"] - rho.max()) <= 9 * 2.0 ** -24 * rho.max()
+
+
+@pytest.mark.parametrize("precision,tx,ty", [("fp32", 120, 102), ("fp64", 78, 78)])
+def test_observables_of_a_buffer_above_4gib(lbm, precision, tx, ty):
+    """The reduction's variant with one buffer resource per lattice row, more tiles than
+    workgroups: a lattice of 100 x 100 copies of a small one (4.4 GB) has its extremes exactly,
+    and 10^4 times its sums, which a lane adds over at most 3 tiles of 40 rows and two trees of 8
+    levels: 150 roundings, 3.3e-14 of the sum of magnitudes, with a factor of ten."""
+    from paper_1412_7228_amd import inputs
+
+    print(f"[gpu-case] observables of {100 * tx} x {100 * ty} {precision}", flush=True)
+    rho = inputs.spinodal(tx, ty, 0.183713, noise=1e-2, seed=12)
+    small = lbm.Lattice(_cfg(tx, ty, precision))
+    small.init_field(rho)
+    small.step(4)
+    f, want = small.fields(), small.observables(check=False)
+    big = lbm.Lattice(_cfg(100 * tx, 100 * ty, precision))
+    big.init_field(np.tile(rho, (100, 100)))
+    big.step(4)
+    for got in (big.observables(check=False), big.observables(check=False, noalloc=True)):
+        for k in ("rho_min", "rho_max", "max_u", "rho_out", "p_out"):
+            assert got[k] == want[k], k
+        assert got["n_nonfinite"] == got["n_domain"] == 0
+        assert abs(got["mass"] - 1e4 * f["rho"].sum()) <= 3.3e-13 * 1e4 * f["rho"].sum()
+        for k, u in (("mom_x", "ux"), ("mom_y", "uy")):
+            m = f["rho"] * f[u]
+            assert abs(got[k] - 1e4 * m.sum()) <= 3.3e-13 * 1e4 * np.abs(m).sum()
+    big.close()
