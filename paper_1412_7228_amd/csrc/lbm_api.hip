@@ -1346,17 +1346,22 @@ size_t batch_largest(const lbm_batch* b) {
 lbm_status batch_scratch(lbm_batch* b) {
   if (b->work) return LBM_OK;
   const size_t largest = batch_largest(b), db = obs_domain_bytes(), lb = obs_block_bytes();
-  long long parts = 0;
-  for (int d = 0; d < b->n; ++d) parts += obs_partials_count(b->g[d]);
+  long long parts = 0, wide = 0;
+  for (int d = 0; d < b->n; ++d) {
+    parts += obs_partials_count(b->g[d]);
+    if (!obs_narrow(b->g[d])) wide += obs_partials_count(b->g[d]);
+  }
   auto whole = [](size_t bytes) { return (bytes + 255) / 256 * 256; };
   const size_t list_at = whole(db * b->n), partials_at = list_at + whole(lb * parts);
   std::unique_ptr<unsigned char[]> h(new (std::nothrow) unsigned char[partials_at]);
   if (!h) return fail(LBM_ENOMEM, "host allocation failed");
-  long long at = 0;
+  long long first = 0, at[2] = {0, wide};  // partials; places in the list
   for (int d = 0; d < b->n; ++d) {
     obs_fill_domain(b->g[d], b->m[d], static_cast<char*>(b->arena) + b->off[0][d],
-                    static_cast<char*>(b->arena) + b->off[1][d], at, h.get() + d * db);
-    for (int k = 0; k < obs_partials_count(b->g[d]); ++k) obs_fill_block(d, k, h.get() + list_at + at++ * lb);
+                    static_cast<char*>(b->arena) + b->off[1][d], first, h.get() + d * db);
+    const int count = obs_partials_count(b->g[d]);
+    for (int k = 0; k < count; ++k) obs_fill_block(d, k, h.get() + list_at + at[obs_narrow(b->g[d])]++ * lb);
+    first += count;
   }
   const size_t fields = whole(4 * largest * sizeof(double)), red = (size_t)b->n * kNumObs;
   char* q = nullptr;
@@ -1370,7 +1375,7 @@ lbm_status batch_scratch(lbm_batch* b) {
   b->work = reinterpret_cast<double*>(q);
   q += fields;
   double* partials = reinterpret_cast<double*>(q + partials_at);
-  b->obs = ObsBatch{q, q + list_at, partials, partials + parts * kNumRed, b->n, parts};
+  b->obs = ObsBatch{q, q + list_at, partials, partials + parts * kNumRed, b->n, parts, wide};
   b->pinned = static_cast<double*>(pinned_memory((stage_doubles(largest) + red) * sizeof(double)));
   if (b->pinned) {
     b->stage = stage_doubles(largest) ? b->pinned : nullptr;

@@ -197,8 +197,15 @@ __device__ inline void block_reduce_store(const double (&acc)[kNumRed], double (
 constexpr int kObsWidth = kRedThreads - 2;
 constexpr int kObsMaxBlocks = 4096;  // blocks beyond take several tiles each
 
+// Lattices of up to this many columns leave most of a tile's lanes idle: there a
+// workgroup takes several tiles, one above the other, side by side in its lanes
+// (obs_tile_narrow): 3 x 140001 FP32 190 us a call with one tile, 32 x 32768 69 us; 64 x
+// 16384, a quarter of the lanes in use, 51 us that way, which hides its loads well enough.
+constexpr int kObsNarrow = 32;
+
 struct ObsTiles {
-  int strips, rows, tiles;  // columns of tiles, rows of a tile, tiles in all
+  int strips, rows, tiles;  // columns of tiles, rows of a tile, tiles (groups of them) in all
+  int groups;               // tiles side by side in a workgroup's lanes (1: wide lattices)
 };
 
 // Rows that give at most 2,048 tiles, two rounds of the four workgroups a CU
@@ -206,10 +213,12 @@ struct ObsTiles {
 // rows, 2,176 tiles); at least 4, and at most 40, beyond which a round's end
 // weighs less than the registers' reuse gains.
 static ObsTiles obs_tiles(const Geometry& g) {
+  const int groups = g.nx <= kObsNarrow ? kRedThreads / (g.nx + 2) : 1;
   const int strips = (g.nx + kObsWidth - 1) / kObsWidth;
-  const int blocks = strips < 2048 ? 2048 / strips : 1;
+  const int blocks = (strips < 2048 ? 2048 / strips : 1) * groups;
   const int most = (g.ny + blocks - 1) / blocks, rows = most < 4 ? 4 : (most > 40 ? 40 : most);
-  return ObsTiles{strips, rows, strips * ((g.ny + rows - 1) / rows)};
+  const int high = rows * groups;
+  return ObsTiles{strips, rows, strips * ((g.ny + high - 1) / high), groups};
 }
 
 template <typename T, int EOS, bool BIG>
@@ -274,26 +283,104 @@ __device__ __forceinline__ void obs_tile(const T* __restrict__ f, const Geometry
   }
 }
 
+// Tiles y0, y0 + H, ... of a narrow lattice side by side, each with the two
+// neighbour columns: obs_tile with the rows its lanes' own.
+template <typename T, int EOS>
+__device__ __forceinline__ void obs_tile_narrow(const T* __restrict__ f, const Geometry& geo, const DevC<double>& c,
+                                                int y0, int H, int groups, ObsSum& sum,
+                                                double2 (*ring)[kRedThreads]) {
+  const int nx = geo.nx, ny = geo.ny, tx = threadIdx.x, wide = nx + 2;
+  const int g = tx / wide, u = tx - g * wide - 1, x = (u + nx) % nx;
+  const int xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
+  const int from = g < groups ? min(y0 + g * H, ny) : ny, h = min(H, ny - from);  // this lane's rows
+  const bool own = u >= 0 && u < nx;
+  const long long pitch = geo.pitch;
+  auto wrap_row = [&](int y) { return y < 0 ? y + ny : (y >= ny ? y - ny : y); };
+  struct Row {
+    double r, U, jx, jy;
+  } now{}, before{};
+  const int n = H + 2;
+  T P[9], Q[9];
+  auto gather_row = [&](int i, T(&q)[9]) {
+    const int y = wrap_row(from - 1 + min(i, h + 1));
+    const T *r = f + (long long)y * geo.row, *m = f + (long long)wrap_row(y - 1) * geo.row,
+            *p = f + (long long)wrap_row(y + 1) * geo.row;
+    q[0] = r[x];
+    q[1] = r[pitch + xm];
+    q[2] = m[2 * pitch + x];
+    q[3] = r[3 * pitch + xp];
+    q[4] = p[4 * pitch + x];
+    q[5] = m[5 * pitch + xm];
+    q[6] = m[6 * pitch + xp];
+    q[7] = p[7 * pitch + xp];
+    q[8] = p[8 * pitch + xm];
+  };
+  gather_row(0, P);
+  gather_row(1, Q);
+  __syncthreads();  // the ring's last readers (the tiles before) are done
+  auto iteration = [&](int i, T(&q)[9]) {
+    double d[9];
+    now.r = 0.0;
+#pragma unroll
+    for (int a = 0; a < 9; ++a) {
+      d[a] = (double)q[a];
+      now.r += d[a];
+    }
+    momentum_core(d, now.jx, now.jy);
+    gather_row(i + 2, q);
+    now.U = eos_U<EOS>(now.r, c);
+    ring[i & 3][tx] = double2{now.U, psi_of(now.U, c)};
+    __syncthreads();
+    if (i >= 2) {
+      const int l = tx == 0 ? 0 : tx - 1, e = tx == kRedThreads - 1 ? tx : tx + 1;  // the rim's lanes add nothing
+      const double2 *nr = ring[i & 3], *mr = ring[(i - 1) & 3], *sr = ring[(i - 2) & 3];
+      const double2 v[9] = {mr[tx], mr[e], nr[tx], mr[l], sr[tx], nr[e], nr[l], sr[l], sr[e]};
+      double Un[9], Pn[9], Fx, Fy;
+#pragma unroll
+      for (int a = 0; a < 9; ++a) {
+        Un[a] = v[a].x;
+        Pn[a] = v[a].y;
+      }
+      force_core(Un, Pn, c, Fx, Fy);
+      accumulate_cell(sum, own && i < h + 2, before.r, before.U, Fx, Fy, before.jx, before.jy);
+    }
+    before = now;
+  };
+#pragma unroll 1
+  for (int i = 0; i < n; i += 2) {
+    iteration(i, P);
+    iteration(i + 1, Q);
+  }
+}
+
+// What a workgroup reads: wide lattices below 4 GiB, above it, narrow ones.
+enum { kObsWhole, kObsBig, kObsColumns };
+
 // Tiles blockIdx.x, blockIdx.x + blocks, ... of one lattice into one partial.
-template <typename T, int EOS, bool BIG>
+template <typename T, int EOS, int FORM>
 __device__ __forceinline__ void obs_block(const T* __restrict__ f, const Geometry& geo, const DevC<double>& c,
                                           const ObsTiles& t, int block, int blocks, double* __restrict__ out) {
   __shared__ double2 ring[4][kRedThreads];
   __shared__ double sh[kNumRed][kRedThreads];
   ObsSum s{0.0, 0.0, 0.0, INFINITY, -INFINITY, 0.0, 0.0, 0u, 0u};
   for (int k = block; k < t.tiles; k += blocks) {
-    const int rb = k / t.strips, y0 = rb * t.rows;
-    obs_tile<T, EOS, BIG>(f, geo, c, (k - rb * t.strips) * kObsWidth, y0, min(t.rows, geo.ny - y0), s, ring);
+    if constexpr (FORM == kObsColumns) {
+      obs_tile_narrow<T, EOS>(f, geo, c, k * t.rows * t.groups, t.rows, t.groups, s, ring);
+    } else {
+      const int rb = k / t.strips, y0 = rb * t.rows;
+      obs_tile<T, EOS, FORM == kObsBig>(f, geo, c, (k - rb * t.strips) * kObsWidth, y0, min(t.rows, geo.ny - y0), s,
+                                        ring);
+    }
   }
   const double acc[kNumRed] = {s.mass, s.mx, s.my, s.lo, s.hi, s.v2, (double)s.n_domain, (double)s.n_bad};
   block_reduce_store(acc, sh, out);
 }
 
-template <typename T, int EOS, bool BIG>
+template <typename T, int EOS, int FORM>
 __global__ void __launch_bounds__(kRedThreads)
     k_obs(const T* __restrict__ f, const Geometry geo, const DevC<double> c, const ObsTiles t,
           double* __restrict__ partials) {
-  obs_block<T, EOS, BIG>(f, geo, c, t, xcd_remap(blockIdx.x, gridDim.x), gridDim.x,
+  obs_block<T, EOS, FORM>(f, geo, c, t, xcd_remap(blockIdx.x, gridDim.x), gridDim.x,
                     partials + (long long)xcd_remap(blockIdx.x, gridDim.x) * kNumRed);
 }
 
@@ -349,13 +436,13 @@ struct ObsBlock {
   int domain, part;
 };
 
-template <typename T, int EOS>
+template <typename T, int EOS, int FORM>
 __global__ void __launch_bounds__(kRedThreads)
     k_batch_obs(const ObsDomain* __restrict__ dom, const ObsBlock* __restrict__ list, int parity,
                 double* __restrict__ partials) {
   const ObsBlock b = list[blockIdx.x];
   const ObsDomain& D = dom[b.domain];
-  obs_block<T, EOS, false>(static_cast<const T*>(D.f[parity]), D.g, D.c, D.t, b.part, D.parts,
+  obs_block<T, EOS, FORM>(static_cast<const T*>(D.f[parity]), D.g, D.c, D.t, b.part, D.parts,
                            partials + (D.first + b.part) * kNumRed);
 }
 
@@ -473,10 +560,12 @@ static hipError_t observables_e(const Geometry& g, const DevC<double>& c, const 
                                 hipStream_t s) {
   const ObsTiles t = obs_tiles(g);
   const int np = obs_partials_count(g);
-  if ((unsigned long long)g.ny * g.row * sizeof(T) < (1ull << 32))
-    hipLaunchKernelGGL((k_obs<T, EOS, false>), dim3(np), dim3(kRedThreads), 0, s, f, g, c, t, partials);
+  if (t.groups > 1)
+    hipLaunchKernelGGL((k_obs<T, EOS, kObsColumns>), dim3(np), dim3(kRedThreads), 0, s, f, g, c, t, partials);
+  else if ((unsigned long long)g.ny * g.row * sizeof(T) < (1ull << 32))
+    hipLaunchKernelGGL((k_obs<T, EOS, kObsWhole>), dim3(np), dim3(kRedThreads), 0, s, f, g, c, t, partials);
   else
-    hipLaunchKernelGGL((k_obs<T, EOS, true>), dim3(np), dim3(kRedThreads), 0, s, f, g, c, t, partials);
+    hipLaunchKernelGGL((k_obs<T, EOS, kObsBig>), dim3(np), dim3(kRedThreads), 0, s, f, g, c, t, partials);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_obs_finish<T>, dim3(1), dim3(kRedThreads), 0, s, f, g, partials, np, red);
@@ -515,31 +604,43 @@ void obs_fill_domain(const Geometry& g, const ModelConsts& m, const void* fa, co
 
 void obs_fill_block(int domain, int part, void* out) { *static_cast<ObsBlock*>(out) = ObsBlock{domain, part}; }
 
-template <typename T>
-static hipError_t batch_observables_t(int eos, const ObsBatch& q, int parity, hipStream_t s) {
+bool obs_narrow(const Geometry& g) { return obs_tiles(g).groups > 1; }
+
+template <typename T, int FORM>
+static hipError_t batch_partials(int eos, const ObsBatch& q, const void* list, long long parts, int parity,
+                                 hipStream_t s) {
   constexpr long long kMost = 1ll << 22;  // workgroups of a launch: its lanes are counted in 32 bits
   const ObsDomain* d = static_cast<const ObsDomain*>(q.domains);
   const dim3 block(kRedThreads);
-  for (long long first = 0; first < q.parts; first += kMost) {
-    const ObsBlock* l = static_cast<const ObsBlock*>(q.list) + first;
-    const dim3 grid((unsigned)(q.parts - first < kMost ? q.parts - first : kMost));
+  for (long long first = 0; first < parts; first += kMost) {
+    const ObsBlock* l = static_cast<const ObsBlock*>(list) + first;
+    const dim3 grid((unsigned)(parts - first < kMost ? parts - first : kMost));
     switch (eos) {
-      case LBM_EOS_IDEAL: hipLaunchKernelGGL((k_batch_obs<T, LBM_EOS_IDEAL>), grid, block, 0, s, d, l, parity, q.partials); break;
-      case LBM_EOS_CS: hipLaunchKernelGGL((k_batch_obs<T, LBM_EOS_CS>), grid, block, 0, s, d, l, parity, q.partials); break;
-      case LBM_EOS_VDW: hipLaunchKernelGGL((k_batch_obs<T, LBM_EOS_VDW>), grid, block, 0, s, d, l, parity, q.partials); break;
-      case LBM_EOS_PR: hipLaunchKernelGGL((k_batch_obs<T, LBM_EOS_PR>), grid, block, 0, s, d, l, parity, q.partials); break;
+      case LBM_EOS_IDEAL: hipLaunchKernelGGL((k_batch_obs<T, LBM_EOS_IDEAL, FORM>), grid, block, 0, s, d, l, parity, q.partials); break;
+      case LBM_EOS_CS: hipLaunchKernelGGL((k_batch_obs<T, LBM_EOS_CS, FORM>), grid, block, 0, s, d, l, parity, q.partials); break;
+      case LBM_EOS_VDW: hipLaunchKernelGGL((k_batch_obs<T, LBM_EOS_VDW, FORM>), grid, block, 0, s, d, l, parity, q.partials); break;
+      case LBM_EOS_PR: hipLaunchKernelGGL((k_batch_obs<T, LBM_EOS_PR, FORM>), grid, block, 0, s, d, l, parity, q.partials); break;
       default: return hipErrorInvalidValue;
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  for (long long first = 0; first < q.n; first += kMost) {
-    const dim3 grid((unsigned)(q.n - first < kMost ? q.n - first : kMost));
-    hipLaunchKernelGGL(k_batch_obs_finish<T>, grid, block, 0, s, d + first, parity, q.partials, q.red + first * kNumObs);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
   return hipSuccess;
+}
+
+template <typename T>
+static hipError_t batch_observables_t(int eos, const ObsBatch& q, int parity, hipStream_t s) {
+  hipError_t e = batch_partials<T, kObsWhole>(eos, q, q.list, q.wide, parity, s);
+  if (e == hipSuccess)
+    e = batch_partials<T, kObsColumns>(eos, q, static_cast<const ObsBlock*>(q.list) + q.wide, q.parts - q.wide, parity, s);
+  constexpr long long kMost = 1ll << 22;
+  for (long long first = 0; first < q.n && e == hipSuccess; first += kMost) {
+    const dim3 grid((unsigned)(q.n - first < kMost ? q.n - first : kMost));
+    hipLaunchKernelGGL(k_batch_obs_finish<T>, grid, dim3(kRedThreads), 0, s, static_cast<const ObsDomain*>(q.domains) + first,
+                       parity, q.partials, q.red + first * kNumObs);
+    e = hipGetLastError();
+  }
+  return e;
 }
 
 hipError_t launch_batch_observables(lbm_precision prec, int eos, const ObsBatch& q, int parity, hipStream_t s) {

@@ -98,14 +98,16 @@ hipError_t launch_observables(lbm_precision prec, const Geometry& g, const Model
 // The observables of every domain of a batch: records of obs_domain_bytes() and
 // a list of its partials (obs_block_bytes() each), filled on the host and copied to
 // the device.  Domain d has obs_partials_count(g) partials, after those of the
-// domains before it.
+// domains before it; the list holds those of the wide domains, then those of the
+// narrow ones (obs_narrow).
 struct ObsBatch {
   const void* domains;
   const void* list;
   double* partials;  // parts * kNumRed
   double* red;       // n * kNumObs
-  long long n, parts;
+  long long n, parts, wide;
 };
+bool obs_narrow(const Geometry& g);
 size_t obs_domain_bytes();
 size_t obs_block_bytes();
 void obs_fill_domain(const Geometry& g, const ModelConsts& m, const void* fa, const void* fb, long long first,
