@@ -197,11 +197,11 @@ __device__ inline void block_reduce_store(const double (&acc)[kNumRed], double (
 constexpr int kObsWidth = kRedThreads - 2;
 constexpr int kObsMaxBlocks = 4096;  // blocks beyond take several tiles each
 
-// Lattices of up to this many columns leave most of a tile's lanes idle: there a
-// workgroup takes several tiles, one above the other, side by side in its lanes
-// (obs_tile_narrow): 3 x 140001 FP32 190 us a call with one tile, 32 x 32768 69 us; 64 x
-// 16384, a quarter of the lanes in use, 51 us that way, which hides its loads well enough.
-constexpr int kObsNarrow = 32;
+// Lattices of up to this many columns leave half of a tile's lanes idle and more: there
+// a workgroup takes two tiles and more, one above the other, side by side in its lanes
+// (obs_tile_narrow).  A call with one tile and so: 3 x 140001 FP32 190 and 53 us, 32 x
+// 32768 69 / 35, 64 x 16384 50 / 37, 100 x 20000 56 / 51, 1,000 domains of 64^2 205 / 124.
+constexpr int kObsNarrow = kRedThreads / 2 - 2;
 
 struct ObsTiles {
   int strips, rows, tiles;  // columns of tiles, rows of a tile, tiles (groups of them) in all

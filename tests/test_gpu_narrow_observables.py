@@ -1,4 +1,4 @@
-"""The observables of narrow lattices (up to 32 columns: several tiles side by side in a workgroup)
+"""The observables of narrow lattices (up to 126 columns: several tiles side by side in a workgroup)
 against the fields they reduce, alone and among wide domains of a batch."""
 import numpy as np
 import pytest
@@ -7,9 +7,10 @@ from test_gpu_observables import _check, lbm  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
-# 3 columns: 51 tiles a workgroup; 32 and 33: the last narrow and the first wide width; rows that leave
-# tiles and workgroups part empty, fewer rows than a workgroup's, more tiles than workgroups
-SIZES = [(3, 3), (3, 203), (3, 204), (3, 9000), (4, 100003), (7, 1000), (16, 40000), (31, 29), (32, 28), (32, 20011), (33, 997)]
+# 3 columns: 51 tiles a workgroup; 126 and 127: the last narrow and the first wide width; 62 and 63: four
+# tiles and three; rows that leave tiles and workgroups part empty, fewer rows than a workgroup's
+SIZES = [(3, 3), (3, 203), (3, 204), (3, 9000), (4, 100003), (7, 1000), (16, 40000), (31, 29), (62, 28), (63, 4011),
+         (126, 9), (126, 5003), (127, 997)]
 
 
 @pytest.mark.parametrize("precision", ["fp32", "fp64"])
@@ -31,7 +32,7 @@ def test_narrow_and_wide_domains_of_a_batch(lbm, precision):  # noqa: F811
     from paper_1412_7228_amd import inputs
 
     print(f"[gpu-case] narrow and wide domains {precision}", flush=True)
-    sizes = [(3, 204), (300, 70), (32, 2011), (33, 50), (5, 5)]
+    sizes = [(3, 204), (300, 70), (32, 2011), (127, 50), (126, 50), (5, 5)]
     cfgs = [dict(nx=x, ny=y, eos="vdw", T_over_Tc=0.9, K=0.3, A=-0.5, kappa=0.2, precision=precision) for x, y in sizes]
     rhos = [inputs.spinodal(x, y, 3.6, noise=1e-2, seed=i) for i, (x, y) in enumerate(sizes)]
     b = lbm.Batch(cfgs)
