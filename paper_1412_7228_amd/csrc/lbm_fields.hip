@@ -417,10 +417,10 @@ __global__ void __launch_bounds__(kRedThreads)
 
 // A batch: one workgroup per partial of every domain, from a list, so that the
 // workspace and the launch grow with the sum over the domains (one 4096^2 among
-// 10,000 of 64^2: 17 MB; records for n times the largest would take 1.1 GB and 18
-// million workgroups).  A domain has the tiles of the same
-// lattice alone, so its observables are those of the lattice bit for bit and do
-// not depend on what else is in the batch.  (Tiles of 16 rows where the batch is
+// 10,000 of 64^2: 10 MB; records for n times the largest would take 1.1 GB and 18
+// million workgroups).  A domain has the tiles of the same lattice alone, so its
+// observables are those of the lattice bit for bit and do not depend on what else
+// is in the batch.  (Tiles of 16 rows where the batch is
 // large read fewer rows twice, a call over 256 domains of 64^2 to 512^2 340 us
 // against 393, and add them in another order.)
 struct ObsDomain {
