@@ -200,7 +200,7 @@ constexpr int kObsMaxBlocks = 4096;  // blocks beyond take several tiles each
 // Lattices of up to this many columns leave half of a tile's lanes idle and more: there
 // a workgroup takes two tiles and more, one above the other, side by side in its lanes
 // (obs_tile_narrow).  A call with one tile and so: 3 x 140001 FP32 190 and 53 us, 32 x
-// 32768 69 / 35, 64 x 16384 50 / 37, 100 x 20000 56 / 51, 1,000 domains of 64^2 205 / 124.
+// 32768 69 / 35, 64 x 16384 50 / 37, 100 x 20000 56 / 49, 1,000 domains of 64^2 205 / 124.
 constexpr int kObsNarrow = kRedThreads / 2 - 2;
 
 struct ObsTiles {
@@ -284,36 +284,50 @@ __device__ __forceinline__ void obs_tile(const T* __restrict__ f, const Geometry
 }
 
 // Tiles y0, y0 + H, ... of a narrow lattice side by side, each with the two
-// neighbour columns: obs_tile with the rows its lanes' own.
-template <typename T, int EOS>
+// neighbour columns: obs_tile with the rows its lanes' own.  They are gathered one
+// after the other at three byte offsets that move on by a row, of 32 bits below 4 GiB:
+// nine 64-bit addresses formed afresh for each row took 71.1 us a call on 64 x 65536 in
+// FP32 where this takes 64.2 (FP64 85.5 / 83.1), 25.2 on 100 x 100 in FP64 (24.8).
+template <typename T, int EOS, typename O>
 __device__ __forceinline__ void obs_tile_narrow(const T* __restrict__ f, const Geometry& geo, const DevC<double>& c,
                                                 int y0, int H, int groups, ObsSum& sum,
                                                 double2 (*ring)[kRedThreads]) {
   const int nx = geo.nx, ny = geo.ny, tx = threadIdx.x, wide = nx + 2;
   const int g = tx / wide, u = tx - g * wide - 1, x = (u + nx) % nx;
-  const int xm = x == 0 ? nx - 1 : x - 1, xp = x == nx - 1 ? 0 : x + 1;
+  const O ox = (O)(x * sizeof(T)), oxm = (O)((x == 0 ? nx - 1 : x - 1) * sizeof(T)),
+          oxp = (O)((x == nx - 1 ? 0 : x + 1) * sizeof(T));
   const int from = g < groups ? min(y0 + g * H, ny) : ny, h = min(H, ny - from);  // this lane's rows
   const bool own = u >= 0 && u < nx;
   const long long pitch = geo.pitch;
   auto wrap_row = [&](int y) { return y < 0 ? y + ny : (y >= ny ? y - ny : y); };
+  const O row = (O)(geo.row * sizeof(T)), end = row * (O)ny;
+  const int first = wrap_row(from - 1);
+  O r = row * (O)first, m = row * (O)wrap_row(first - 1), p = row * (O)wrap_row(first + 1);
   struct Row {
     double r, U, jx, jy;
   } now{}, before{};
   const int n = H + 2;
   T P[9], Q[9];
+  auto load = [&](int a, O o) {
+    return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(f + a * pitch) + o);
+  };
+  // row from - 1 + min(i, h + 1), for i = 0, 1, 2, ... in turn
   auto gather_row = [&](int i, T(&q)[9]) {
-    const int y = wrap_row(from - 1 + min(i, h + 1));
-    const T *r = f + (long long)y * geo.row, *m = f + (long long)wrap_row(y - 1) * geo.row,
-            *p = f + (long long)wrap_row(y + 1) * geo.row;
-    q[0] = r[x];
-    q[1] = r[pitch + xm];
-    q[2] = m[2 * pitch + x];
-    q[3] = r[3 * pitch + xp];
-    q[4] = p[4 * pitch + x];
-    q[5] = m[5 * pitch + xm];
-    q[6] = m[6 * pitch + xp];
-    q[7] = p[7 * pitch + xp];
-    q[8] = p[8 * pitch + xm];
+    q[0] = load(0, r + ox);
+    q[1] = load(1, r + oxm);
+    q[2] = load(2, m + ox);
+    q[3] = load(3, r + oxp);
+    q[4] = load(4, p + ox);
+    q[5] = load(5, m + oxm);
+    q[6] = load(6, m + oxp);
+    q[7] = load(7, p + oxp);
+    q[8] = load(8, p + oxm);
+    if (i <= h) {
+      m = r;
+      r = p;
+      p += row;
+      if (p == end) p = 0;
+    }
   };
   gather_row(0, P);
   gather_row(1, Q);
@@ -353,8 +367,8 @@ __device__ __forceinline__ void obs_tile_narrow(const T* __restrict__ f, const G
   }
 }
 
-// What a workgroup reads: wide lattices below 4 GiB, above it, narrow ones.
-enum { kObsWhole, kObsBig, kObsColumns };
+// What a workgroup reads: wide lattices below 4 GiB and above it, narrow ones below and above.
+enum { kObsWhole, kObsBig, kObsColumns, kObsColumnsBig };
 
 // Tiles blockIdx.x, blockIdx.x + blocks, ... of one lattice into one partial.
 template <typename T, int EOS, int FORM>
@@ -365,7 +379,9 @@ __device__ __forceinline__ void obs_block(const T* __restrict__ f, const Geometr
   ObsSum s{0.0, 0.0, 0.0, INFINITY, -INFINITY, 0.0, 0.0, 0u, 0u};
   for (int k = block; k < t.tiles; k += blocks) {
     if constexpr (FORM == kObsColumns) {
-      obs_tile_narrow<T, EOS>(f, geo, c, k * t.rows * t.groups, t.rows, t.groups, s, ring);
+      obs_tile_narrow<T, EOS, unsigned>(f, geo, c, k * t.rows * t.groups, t.rows, t.groups, s, ring);
+    } else if constexpr (FORM == kObsColumnsBig) {
+      obs_tile_narrow<T, EOS, unsigned long long>(f, geo, c, k * t.rows * t.groups, t.rows, t.groups, s, ring);
     } else {
       const int rb = k / t.strips, y0 = rb * t.rows;
       obs_tile<T, EOS, FORM == kObsBig>(f, geo, c, (k - rb * t.strips) * kObsWidth, y0, min(t.rows, geo.ny - y0), s,
@@ -560,9 +576,12 @@ static hipError_t observables_e(const Geometry& g, const DevC<double>& c, const 
                                 hipStream_t s) {
   const ObsTiles t = obs_tiles(g);
   const int np = obs_partials_count(g);
-  if (t.groups > 1)
+  const bool big = (unsigned long long)g.ny * g.row * sizeof(T) >= (1ull << 32);
+  if (t.groups > 1 && big)
+    hipLaunchKernelGGL((k_obs<T, EOS, kObsColumnsBig>), dim3(np), dim3(kRedThreads), 0, s, f, g, c, t, partials);
+  else if (t.groups > 1)
     hipLaunchKernelGGL((k_obs<T, EOS, kObsColumns>), dim3(np), dim3(kRedThreads), 0, s, f, g, c, t, partials);
-  else if ((unsigned long long)g.ny * g.row * sizeof(T) < (1ull << 32))
+  else if (!big)
     hipLaunchKernelGGL((k_obs<T, EOS, kObsWhole>), dim3(np), dim3(kRedThreads), 0, s, f, g, c, t, partials);
   else
     hipLaunchKernelGGL((k_obs<T, EOS, kObsBig>), dim3(np), dim3(kRedThreads), 0, s, f, g, c, t, partials);
