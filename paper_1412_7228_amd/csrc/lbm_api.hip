@@ -342,7 +342,7 @@ struct lbm_ctx {
   double* work;      // device: 4 * nx*ny (rho, U, psi, out), then the partials and kNumObs
   double* partials;  // obs_partials_count * kNumRed
   double* pinned;    // host memory that the kernels read and write (may be null): the stage, then red
-  double* stage;     // small lattices: 3 * nx*ny (see kStageCells)
+  double* stage;     // small lattices: stage_doubles(nx*ny)
   double* red;       // kNumObs, in pinned memory or on the device
 };
 
@@ -500,8 +500,15 @@ void* pinned_memory(size_t bytes) {
   return nullptr;
 }
 
-// Doubles of pinned memory that stage fields of up to `cells` cells.
-size_t stage_doubles(size_t cells) { return cells <= kStageCells ? 3 * cells : 0; }
+// Doubles of pinned memory that stage fields of up to `cells` cells: one field, and of
+// small ones the three of an initial state.  The first write of a fresh pinned page takes
+// 1 to 2 us, a copy to a device array 10 us and its bytes' share: the first state with
+// velocities of a 300^2 lattice 1.08 ms with three staged fields and 0.61 with one (500^2
+// 2.8 and 1.4), repeated 169 us and 171; of 100^2 repeated 31 us with three, 48 with one.
+size_t stage_doubles(size_t cells) {
+  constexpr size_t kThree = 3u << 14;
+  return cells <= kStageCells ? std::max(cells, std::min(3 * cells, kThree)) : 0;
+}
 
 // Allocates the scratch of the fields and the observables, so that no later call
 // does: one device allocation and one of pinned memory (each costs an allocation and a
@@ -642,16 +649,18 @@ lbm_status read_field(const lbm_params& p, const ModelConsts& m, const Geometry&
   return LBM_OK;
 }
 
-// Initial densities and velocities (ux, uy may be null) of one lattice into f.
+// Initial densities and velocities (ux, uy may be null) of one lattice into f; those that
+// the stage of `room` doubles does not hold go through the device's work.
 lbm_status write_initial(const lbm_params& p, const Geometry& g, const double* rho, const double* ux,
-                         const double* uy, double* work, double* stage, void* f, hipStream_t stream) {
+                         const double* uy, double* work, double* stage, size_t room, void* f, hipStream_t stream) {
   const size_t n = (size_t)p.nx * p.ny;
   const double* from[3] = {rho, ux, uy};
   double* to[3] = {};
   for (int k = 0; k < 3; ++k) {
     if (!from[k]) continue;
-    to[k] = (stage ? stage : work) + k * n;
-    if (stage)
+    const bool staged = stage && (k + 1) * n <= room;
+    to[k] = (staged ? stage : work) + k * n;
+    if (staged)
       std::memcpy(to[k], from[k], n * sizeof(double));
     else
       HIP_TRY(hipMemcpyAsync(to[k], from[k], n * sizeof(double), hipMemcpyHostToDevice, stream));
@@ -849,7 +858,8 @@ lbm_status lbm_init_field(lbm_ctx* c, const double* rho, const double* ux, const
   if (st != LBM_OK) return st;
   if ((st = ensure_scratch(c)) != LBM_OK) return st;
   c->cur = 0;
-  if ((st = write_initial(c->p, c->g, rho, ux, uy, c->work, c->stage, c->buf[0], c->stream)) != LBM_OK) return st;
+  if ((st = write_initial(c->p, c->g, rho, ux, uy, c->work, c->stage,
+                          stage_doubles((size_t)c->p.nx * c->p.ny), c->buf[0], c->stream)) != LBM_OK) return st;
   c->step = 0;
   c->pending = 0;
   c->initialized = true;
@@ -1088,7 +1098,7 @@ struct lbm_batch {
   double* work = nullptr;    // device: 4 fields of the largest domain, then the arrays of `obs`
   ObsBatch obs{};
   double* pinned = nullptr;  // host memory that the kernels read and write (may be null): the stage, then obs.red
-  double* stage = nullptr;   // 3 fields of the largest domain (see kStageCells)
+  double* stage = nullptr;   // stage_doubles of the largest domain
 };
 
 namespace {
@@ -1541,7 +1551,8 @@ lbm_status lbm_batch_init_field(lbm_batch* b, int32_t i, const double* rho, cons
   if ((st = batch_scratch(b)) != LBM_OK) return st;
   HIP_TRY(hipStreamSynchronize(b->stream));
   void* f = static_cast<char*>(b->arena) + b->off[b->parity][i];
-  if ((st = write_initial(b->p[i], b->g[i], rho, ux, uy, b->work, b->stage, f, b->stream)) != LBM_OK) return st;
+  if ((st = write_initial(b->p[i], b->g[i], rho, ux, uy, b->work, b->stage,
+                          stage_doubles(batch_largest(b)), f, b->stream)) != LBM_OK) return st;
   b->inited[i] = true;
   return LBM_OK;
 }
